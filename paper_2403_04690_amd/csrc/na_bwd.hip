@@ -83,7 +83,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
     const int tstep = g.d[R - 1];
     typename C::Ld ld;
     auto issue_stage = [&](int s, int buf) {
-        ld.compute(halo, s * SB, tstep, wave, lane);
+        ld.template compute<false>(halo, s * SB, tstep, wave, lane);
         unsigned char* tile = smem_raw + buf * C::kBufBytes;
         ld.issue(kb, tile, wave);
         ld.issue(vb, tile + C::kTileBytes, wave);
@@ -419,7 +419,7 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
     bool row_ok = false;
     i32x4 orow[L::kSegs];  // kRegDelta: this thread's O row
     auto issue_stage = [&](int s, int buf) {
-        ld.compute(ibox, s * SB, tstep, wave, lane);
+        ld.template compute<false>(ibox, s * SB, tstep, wave, lane);
         unsigned char* tile = smem_raw + buf * C::kBufBytes;
         ld.issue(qb, tile, wave);
         ld.issue(gb, tile + C::kTileBytes, wave);

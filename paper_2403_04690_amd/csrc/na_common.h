@@ -8,6 +8,18 @@
 // The contraction only needs A and B to agree on which real index sits in
 // each slot, so the kernels freely permute slots.  fp32 runs the same 16x16x32
 // step as eight v_mfma_f32_16x16x4_f32 instructions (one slot each).
+//
+// 16-bit kernels with 32 tokens per wave use v_mfma_f32_32x32x16_{f16,bf16}:
+//   operand A (32 x 16): lane l holds row (l % 32), slots 8*(l/32) .. +7
+//   operand B (16 x 32): lane l holds column (l % 32), the same 8 slots
+//   result  C (32 x 32): lane l holds column (l % 32), entry i is row
+//                        8*(i/4) + 4*(l/32) + i%4
+// A 32x32x16 step does the work of four 16x16x16 ones and keeps the matrix
+// core busy for 32 cycles per issue instead of 16, which leaves the issue slots
+// between for VALU work.  Measured on independent streams, four waves per SIMD:
+// 16 exponentials and 24 FMAs beside the products of a 32 x 32 tile at D = 64
+// take 147-166 ns with 32x32x16 steps (the products alone take 150) and
+// 192-196 ns with 16x16x32 ones.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -27,6 +39,7 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -46,6 +59,9 @@ struct Tr<_Float16> {
     __device__ static f32x4 mma(x8 a, x8 b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
     }
+    __device__ static f32x16 mma(x8 a, x8 b, f32x16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+    }
     __device__ static _Float16 cvt(float x) { return (_Float16)x; }
 };
 
@@ -56,6 +72,9 @@ struct Tr<__bf16> {
     static constexpr int kVec = 8;
     __device__ static f32x4 mma(x8 a, x8 b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+    __device__ static f32x16 mma(x8 a, x8 b, f32x16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     }
     __device__ static __bf16 cvt(float x) { return (__bf16)x; }
 };
@@ -118,6 +137,36 @@ __device__ __forceinline__ typename Tr<T>::x8 zero_x8() {
     return typename Tr<T>::x8{};
 }
 
+// Result tile of 32 tokens (rows) x Q tokens (columns): what a wave holds of
+// one pair of 16-token row blocks.  Lane l has column l % Q and, of row block
+// bi, kN rows: entry r is row score_row(r, l / Q) of the block.
+template <int Q>
+struct Tile;
+template <>
+struct Tile<16> {
+    static constexpr int kN = 4;
+    f32x4 b[2];
+    __device__ __forceinline__ float at(int bi, int r) const { return b[bi][r]; }
+    __device__ __forceinline__ void set(int bi, int r, float x) { b[bi][r] = x; }
+};
+template <>
+struct Tile<32> {
+    static constexpr int kN = 8;
+    f32x16 v;
+    __device__ __forceinline__ float at(int bi, int r) const { return v[bi * 8 + r]; }
+    __device__ __forceinline__ void set(int bi, int r, float x) { v[bi * 8 + r] = x; }
+};
+template <int Q>
+__device__ __forceinline__ Tile<Q> splat_tile(float x) {
+    Tile<Q> t;
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int r = 0; r < Tile<Q>::kN; ++r) t.set(bi, r, x);
+    return t;
+}
+__device__ __forceinline__ int score_row(int r, int grp) { return (r >> 2) * 8 + grp * 4 + (r & 3); }
+
 // Store four fp32 values rounded to T at p (8 or 16 bytes).
 template <typename T>
 __device__ __forceinline__ void st_x4(T* p, f32x4 v) {
@@ -150,15 +199,30 @@ __device__ __forceinline__ float group_sum4(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// The same over the lanes holding one column of a Q-column result tile: all
+// four groups (Q = 16), or the two halves of the wave (Q = 32).
+template <int Q>
+__device__ __forceinline__ float col_max(float x) {
+    if constexpr (Q == 16) return group_max4(x);
+    const unsigned v = __float_as_uint(x);
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+template <int Q>
+__device__ __forceinline__ float col_sum(float x) {
+    if constexpr (Q == 16) return group_sum4(x);
+    const unsigned v = __float_as_uint(x);
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // acc + sum of the 8 probabilities of a P fragment.  16-bit types sum the
 // rounded values the matrix product uses, two at a time (v_dot2 with 1.0);
 // fp32 sums the values themselves.
 template <typename T>
-__device__ __forceinline__ float row_sum8(typename Tr<T>::x8 pf, const float (&p)[2][4],
-                                          float acc) {
+__device__ __forceinline__ float row_sum8(typename Tr<T>::x8 pf, float acc) {
     if constexpr (sizeof(T) == 4) {
-        return acc + ((p[0][0] + p[0][1]) + (p[0][2] + p[0][3])) +
-               ((p[1][0] + p[1][1]) + (p[1][2] + p[1][3]));
+        return acc + ((pf[0] + pf[1]) + (pf[2] + pf[3])) + ((pf[4] + pf[5]) + (pf[6] + pf[7]));
     } else {
         typedef T t2 __attribute__((ext_vector_type(2)));
         const t2 one = {(T)1.0f, (T)1.0f};
@@ -196,6 +260,12 @@ __device__ __forceinline__ float dot8(typename Tr<T>::x8 a, typename Tr<T>::x8 b
     }
 }
 
+// acc + a b of one bf16 32x32x16 step whatever the kernel's type (mask products).
+__device__ __forceinline__ f32x16 mma_bf16(i32x4 a, i32x4 b, f32x16 acc) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Problem geometry shared by all kernels (filled on the host).  Axes beyond
@@ -217,6 +287,7 @@ struct Geo {
     int lgWGd[kMaxRank]; // log2 WGd
     FastDiv fd_ntiles, fd_ngroups, fd_d[kMaxRank], fd_nt[kMaxRank];
     int bwd_split;       // backward only: run as the split form (chosen on the host)
+    int tab_off, tab_rows;  // narrow form only: LDS offset and rows of each mask table
 };
 
 // Brings the Geo fields of the problem's R axes into scalar registers in one

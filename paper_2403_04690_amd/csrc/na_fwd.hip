@@ -43,35 +43,35 @@ namespace na {
 
 constexpr float kLazy = 8.f;  // base-2 headroom before the running max is raised
 
-template <int R, int D, typename T, int QM, int SB, int W = 4>
+template <int R, int D, typename T, int SB, int W = 4>
 struct FwdCfg {
     static constexpr int kWaves = W;
     static constexpr int kThreads = W * kWave;
     static constexpr int kKeys = SB * 16;  // keys per stage
     static constexpr int kTileBytes = kKeys * Rows<T, D>::kRowBytes;
     static constexpr size_t kBufBytes = 2 * kTileBytes;  // K rows, then V rows
-    static constexpr int kKS = D / 32;  // contraction steps over D
-    static constexpr int kDB = D / 16;  // 16-wide blocks of D
     using Ld = DirectRows<T, D, kKeys, W, (R > 1)>;
     static_assert(SB % 2 == 0 && SB <= 32, "stage blocks are tested by one lane each");
 };
 
-// Workgroups per CU the register allocation must allow: four waves per SIMD
-// for the 16-bit kernels that fit 128 VGPRs (every one at D <= 64, and the
-// one-block ones at D = 128); the others take what they need.
-template <int D, typename T, int QM, int W>
-constexpr int fwd_min_blocks() {
-    return sizeof(T) == 2 && (D <= 64 || QM == 1) ? 16 / W : 1;
+// Waves per SIMD the register allocation must allow: four for the 16-bit
+// kernels that fit 128 VGPRs (every one at D <= 64, and the one-block ones at
+// D = 128); the others take what they need.
+template <int D, typename T, int Q, int QM>
+constexpr int fwd_min_waves() {
+    return sizeof(T) == 2 && (D <= 64 || (Q == 16 && QM == 1)) ? 4 : 1;
 }
 
 // c = scale * log2(e): scores are kept in base 2.  SHORT = 1: every halo row
 // holds at most two 16-key blocks (rank >= 2), so the inner-axis mask is a
 // per-lane constant; SHORT = 0: general masking with mask-free full blocks.
-template <int R, int D, typename T, int QM, int SB, int SHORT, int W>
-__global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na_fwd_kernel(
+template <int R, int D, typename T, int Q, int QM, int SB, int SHORT, int W>
+__global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_fwd_kernel(
     Geo g, const T* __restrict__ qg, const T* __restrict__ kg, const T* __restrict__ vg,
     T* __restrict__ og, float* __restrict__ lseg, float c) {
-    using C = FwdCfg<R, D, T, QM, SB, W>;
+    using C = FwdCfg<R, D, T, SB, W>;
+    constexpr bool kNar = SHORT == 2;  // narrow form
+    using Ops = TileOps<T, D, Q, kNar>;
     using x8 = typename Tr<T>::x8;
     extern __shared__ __align__(16) unsigned char smem_raw[];
 
@@ -80,8 +80,8 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
     // (masked: the launch has W waves, which lets the compiler drop the
     // staging loops' bounds tests)
     const int wave = uniform((tid >> 6) & (W - 1));
-    const int col = lane & 15;  // query column of this lane
-    const int grp = lane >> 4;  // 16-lane group
+    const int col = lane & (Q - 1);  // query column of this lane
+    const int grp = lane / Q;        // Q-lane group
 
     // ---- workgroup -> (bh, dilation group, tile) ----
     fetch_geo<R>(g);
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
     // loads are in flight during the per-wave and per-lane set-up below.
     typename C::Ld ld;
     auto issue_stage = [&](int s, int buf) {
-        ld.compute(halo, s * SB, tstep, wave, lane);
+        ld.template compute<kNar>(halo, s * SB, tstep, wave, lane);
         unsigned char* tile = smem_raw + buf * C::kBufBytes;
         ld.issue(kb, tile, wave);
         ld.issue(vb, tile + C::kTileBytes, wave);
@@ -124,6 +124,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
     unravel_pow2<R>(wave, g.lgWGd, wc);
     bool wave_live = true;
     WaveRange<R> wr;
+    int nlow[kMaxRank], nfirst[kMaxRank];  // narrow form: see MaskRows
 #pragma unroll
     for (int a = 0; a < R; ++a) {
         wo[a] = to[a] + wc[a] * g.WT[a];
@@ -134,17 +135,26 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
         const int sf = win_start(f, n[a], g.k[a], ca), sl = win_start(l, n[a], g.k[a], ca);
         const int ef = win_last(f, n[a], g.k[a], ca), el = win_last(l, n[a], g.k[a], ca);
         wr.set(a, sf - halo.lo[a], el + 1 - halo.lo[a], sl - halo.lo[a], ef + 1 - halo.lo[a]);
+        nlow[a] = sl - sf;
+        nfirst[a] = ef + 1 - sf;
+    }
+    const int col0 = kNar ? min(wr.lo[R - 1], 8) : 0;  // narrow form: the wave's first column
+    MaskRows<R> mrows;
+    if constexpr (kNar) {
+        mrows.init(g, wr, nlow, nfirst);
+        if ((wave & (g.WGd[R - 1] - 1)) == 0 && wave_live)
+            mrows.write_table(g, halo, smem_raw + g.tab_off, wave >> g.lgWGd[R - 1], lane);
     }
 
     // ---- per-lane queries: validity, window starts (relative to the halo), Q ----
     int qs[QM][kMaxRank];
     bool qvalid[QM];
     size_t qoff[QM];
-    x8 qf[QM][C::kKS];
+    x8 qf[QM][Ops::kKS];
 #pragma unroll
     for (int m = 0; m < QM; ++m) {
         int cc[kMaxRank];
-        unravel_pow2<R>(m * 16 + col, g.lgWT, cc);
+        unravel_pow2<R>(m * Q + col, g.lgWT, cc);
         bool ok = wave_live;
         int tok = 0;
 #pragma unroll
@@ -160,21 +170,30 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
 #pragma unroll
         // unconditional: qoff points at a real (clamped) query even for absent
         // slots, whose results are discarded; no wait before the K/V loads
-        for (int s = 0; s < C::kKS; ++s) qf[m][s] = ld_x8<T>(qg + qoff[m] + s * 32 + grp * 8);
+        for (int s = 0; s < Ops::kKS; ++s)
+            qf[m][s] = ld_x8<T>(qg + qoff[m] + s * Ops::kStep + grp * 8);
     }
 
-    RowFrag<T, D> kfr;
-    ColFrag<T, D> vfr;
-    kfr.init(lane);
-    vfr.init(lane);
+    Ops ops;
+    ops.init(lane, col0);
+    i32x4 pen{};  // narrow form: this lane's mask operand
+    unsigned tab_lane = 0;
+    if constexpr (kNar) {
+        pen = mrows.query_operand(g, qs[0], grp);
+        tab_lane = g.tab_off + (wave >> g.lgWGd[R - 1]) * g.tab_rows * 32 + (col >> 3) * 32 +
+                   grp * 16;
+    }
 
     // ---- online-softmax state (per lane: its query column) ----
+    // kNoRef: thr before the row has a reference; the narrow form's masked scores
+    // are finite, at most kMasked, and must stay below it.
+    constexpr float kNoRef = kNar ? 0.5f * kMasked : -INFINITY;
     // mref: running reference (base 2, -inf until the row sees a key);
     // negm = -mref (0 while mref = -inf) is the scores' addend and thr the
     // score above which the reference must be raised.
-    // Row sums: with kMfmaSum, lsum[m] accumulates ones^T P^T on the matrix
-    // cores (every entry is the row sum); otherwise each lane sums its share
-    // of P in lrow[m], reduced across the four lane groups at the end.
+    // Row sums: with kMfmaSum, lsum[m] accumulates the row sums of the rounded
+    // P on the matrix cores; otherwise each lane sums its share of P in
+    // lrow[m], reduced across the lane groups at the end.
     // Two blocks per wave: the matrix cores at D = 32, and in 1-D at D = 64,
     // where the two extra accumulators leave the occupancy as it is
     // (elsewhere they cost a wave per SIMD).
@@ -183,9 +202,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
     // addend vectors would cost it occupancy) nor bf16 (rounding c*Q to 8
     // mantissa bits would add an error comparable to that of P itself).
     constexpr bool kFoldAdd = D <= 64 && !std::is_same_v<T, __bf16>;
-    x8 ones;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) ones[j] = (T)1.0f;
+    x8 ones = Ops::ones_frag(lane);
     // kept in four registers for the whole loop: rebuilt from the constant
     // it would cost three moves per tile
     if constexpr (kMfmaSum) {
@@ -193,7 +210,8 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
         asm volatile("" : "+v"(u));
         ones = __builtin_bit_cast(x8, u);
     }
-    f32x4 oacc[QM][C::kDB], lsum[QM];
+    typename Ops::Acc oacc[QM][Ops::kDB];
+    f32x4 lsum[QM];
     float mref[QM], negm[QM], thr[QM], lrow[QM];
     // kFoldAdd: negm in all four slots, the accumulator seed of full tiles,
     // kept as a vector so the matrix cores read it in place (no per-tile splat)
@@ -203,31 +221,32 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
         mref[m] = -INFINITY;
         negm[m] = 0.f;
         negm4[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-        thr[m] = -INFINITY;
+        thr[m] = kNoRef;
         lsum[m] = f32x4{0.f, 0.f, 0.f, 0.f};
         lrow[m] = 0.f;
 #pragma unroll
-        for (int db = 0; db < C::kDB; ++db) oacc[m][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int db = 0; db < Ops::kDB; ++db) oacc[m][db] = typename Ops::Acc{} * 0.f;
     }
     // Halo rows of at most two 16-key blocks (the usual 2-D / 3-D case): the
-    // inner-axis test of this lane's 4 key slots is fixed for the whole
+    // inner-axis test of this lane's key slots is fixed for the whole
     // kernel, so it is folded into per-slot FMA addends (negm where valid,
     // -inf where not), refreshed only when the reference moves.  Block bi of
     // a tile has inner block index bi when rows hold two blocks, else 0.
     constexpr bool short_rows = SHORT != 0 && R > 1;
-    f32x4 ain[QM][2];
+    // (the narrow form's tiles hold the wave's eight columns of four rows)
+    Tile<Q> ain[QM];
     auto refresh_addends = [&](int m) {
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < Tile<Q>::kN; ++r) {
                 const int ib = halo.nbr == 2 ? bi : 0;
-                const bool v =
-                    (unsigned)(ib * 16 + grp * 4 + r - qs[m][R - 1]) < (unsigned)g.k[R - 1];
-                ain[m][bi][r] = v ? negm[m] : -INFINITY;
+                const int pos = kNar ? col0 + grp * 4 + (r & 3) : ib * 16 + score_row(r, grp);
+                const bool v = (unsigned)(pos - qs[m][R - 1]) < (unsigned)g.k[R - 1];
+                ain[m].set(bi, r, v ? negm[m] : -INFINITY);
             }
     };
-    if (R > 1) {
+    if (short_rows) {
 #pragma unroll
         for (int m = 0; m < QM; ++m) refresh_addends(m);
     }
@@ -242,7 +261,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
 #pragma unroll
     for (int m = 0; m < QM; ++m)
 #pragma unroll
-        for (int st = 0; st < C::kKS; ++st)
+        for (int st = 0; st < Ops::kKS; ++st)
 #pragma unroll
             for (int j = 0; j < 8; ++j) qf[m][st][j] = Tr<T>::cvt((float)qf[m][st][j] * c);
 
@@ -250,7 +269,6 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
     for (int s = 0; s < nst; ++s) {
         if (s + 1 < nst) issue_stage(s + 1, (s + 1) & 1);
         const unsigned char* ks = smem_raw + (s & 1) * C::kBufBytes;
-        const unsigned char* vs = ks + C::kTileBytes;
 
         if (wave_live) {
             // the halo's blocks are tested against this wave's queries (one
@@ -262,6 +280,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
             const uint64_t fullm = ct.full_bits();
             const uint64_t ofullm = ct.ofull_bits();
             uint64_t tiles = (relm | (relm >> 1)) & 0x5555555555555555ull;
+            if constexpr (kNar) tiles = (tiles | (tiles >> 2)) & 0x1111111111111111ull;
             // The body of one tile (block pair tp), by kind: 0 general; 1 both
             // blocks inside every window of the wave's queries (no mask); 2 short
             // rows, both blocks inside every window along the outer axes (the
@@ -291,20 +310,14 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
                 // stand-in rows).  The V fragments of the tile are read here
                 // too (D = 32), so one LDS round trip serves the whole tile.
                 constexpr int kRowB = Rows<T, D>::kRowBytes;
-                x8 kf[2][C::kKS];
-#pragma unroll
-                for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                    for (int st = 0; st < C::kKS; ++st)
-                        kf[bi][st] = kfr.read(ks + (tp * 2 + bi) * 16 * kRowB, st);
-                constexpr bool kEarlyV = D == 32;
-                x8 vf[C::kDB];
-                auto read_v = [&]() {
-#pragma unroll
-                    for (int db = 0; db < C::kDB; ++db)
-                        vf[db] = vfr.read(vs + tp * 32 * kRowB, db, lane);
-                };
-                if (kEarlyV) read_v();
+                const unsigned char* kt = ks + tp * 32 * kRowB;
+                x8 kf[Ops::kF];
+                ops.rows(kt, kf);
+                constexpr bool kEarlyV = D == 32 && Q == 16;
+                constexpr bool kMidV = D <= 64 && Q == 32;
+                x8 vf[Ops::kF];
+                if (kEarlyV) ops.template cols<C::kTileBytes>(kt, vf);
+                if (Q == 32) __builtin_amdgcn_sched_barrier(0);
                 // ---- Y^T = c K Q^T + A, A the addend: -m on valid pairs, -inf on masked ----
                 // (base 2, relative to the running reference m).  With kFoldAdd the
                 // accumulator starts at A and Q is prescaled, so the matrix cores
@@ -327,109 +340,127 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
                         const unsigned lim = outer_ok ? (unsigned)g.k[R - 1] : 0u;
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            add[r] = short_rows ? (outer_ok ? ain[m][bi][r] : -INFINITY)
+                            add[r] = short_rows ? (outer_ok ? ain[m].at(bi, r) : -INFINITY)
                                      : (unsigned)(base + r) < lim ? negm[m] : -INFINITY;
                     }
                     return add;
                 };
-                f32x4 sacc[QM][2];
-#pragma unroll
-                for (int bi = 0; bi < 2; ++bi)
+                Tile<Q> sacc[QM], addt[QM];
+                if constexpr (kNar) {
+                    // the inner-axis addends, plus what the outer axes mask
+                    const i32x4 rows = lds16(smem_raw + tab_lane + (s * SB + tp * 2) * 32);
 #pragma unroll
                     for (int m = 0; m < QM; ++m) {
-                        // (the first product of a full tile reads negm4 in place, of an
-                        // outer-full tile of short rows the inner addends)
-                        if (kFoldAdd && !short_rows && full[bi])
-                            sacc[m][bi] = Tr<T>::mma(kf[bi][0], qf[m][0], negm4[m]);
-                        else if (kFoldAdd && short_rows && kOF[bi])
-                            sacc[m][bi] = Tr<T>::mma(kf[bi][0], qf[m][0], ain[m][bi]);
-                        else
-                            sacc[m][bi] = Tr<T>::mma(kf[bi][0], qf[m][0],
-                                                     kFoldAdd ? score_addend(m, bi)
-                                                              : f32x4{0.f, 0.f, 0.f, 0.f});
+                        addt[m].v = mma_bf16(rows, pen, ain[m].v);
+                        sacc[m] = kFoldAdd ? addt[m] : splat_tile<Q>(0.f);
 #pragma unroll
-                        for (int st = 1; st < C::kKS; ++st)
-                            sacc[m][bi] = Tr<T>::mma(kf[bi][st], qf[m][st], sacc[m][bi]);
+                        for (int n_ = 0; n_ < Ops::kF; ++n_)
+                            Ops::score(sacc[m], kf[n_], n_, qf[m]);
                     }
+                } else {
+#pragma unroll
+                    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                        for (int m = 0; m < QM; ++m) {
+                            const int n0 = bi * Ops::kKS;
+                            // (the first product of a full tile reads negm4 in place, of an
+                            // outer-full tile of short rows the inner addends)
+                            if (kFoldAdd && !short_rows && full[bi])
+                                sacc[m].b[bi] = Tr<T>::mma(kf[n0], qf[m][0], negm4[m]);
+                            else if (kFoldAdd && short_rows && kOF[bi])
+                                sacc[m].b[bi] = Tr<T>::mma(kf[n0], qf[m][0], ain[m].b[bi]);
+                            else
+                                sacc[m].b[bi] = Tr<T>::mma(kf[n0], qf[m][0],
+                                                           kFoldAdd ? score_addend(m, bi)
+                                                                    : f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                            for (int n_ = n0 + 1; n_ < n0 + Ops::kKS; ++n_)
+                                Ops::score(sacc[m], kf[n_], n_, qf[m]);
+                        }
+                }
+                if (kMidV) ops.template cols<C::kTileBytes>(kt, vf);
 
                 // ---- online softmax per query block ----
-                x8 pf[QM];
+                x8 pf[QM][Ops::kPF];
 #pragma unroll
                 for (int m = 0; m < QM; ++m) {
-                    float y[2][4];
+                    constexpr int kN = Tile<Q>::kN;
+                    float y[2][kN];
+                    if constexpr (kFoldAdd) {
 #pragma unroll
-                    for (int bi = 0; bi < 2; ++bi) {
-                        if constexpr (kFoldAdd) {
+                        for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) y[bi][r] = sacc[m][bi][r];
-                        } else {
-                            const f32x4 add = score_addend(m, bi);
+                            for (int r = 0; r < kN; ++r) y[bi][r] = sacc[m].at(bi, r);
+                    } else {
+                        if constexpr (!kNar)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) y[bi][r] = fmaf(sacc[m][bi][r], c, add[r]);
-                        }
+                            for (int bi = 0; bi < 2; ++bi) addt[m].b[bi] = score_addend(m, bi);
+#pragma unroll
+                        for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                            for (int r = 0; r < kN; ++r)
+                                y[bi][r] = fmaf(sacc[m].at(bi, r), c, addt[m].at(bi, r));
                     }
                     // this lane's share of the row; the row maximum exceeds the
                     // threshold exactly when some lane's share does
-                    // (a chain, so that it becomes three v_max3 and one v_max)
-                    const float lmax = fmaxf(
-                        fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(y[0][0], y[0][1]), y[0][2]), y[0][3]),
-                                          y[1][0]),
-                                    y[1][1]),
-                              y[1][2]),
-                        y[1][3]);
+                    // (a chain, so that it becomes v_max3 instructions)
+                    float lmax = y[0][0];
+#pragma unroll
+                    for (int r = 1; r < 2 * kN; ++r) lmax = fmaxf(lmax, y[r / kN][r % kN]);
                     // raise the reference on the first valid key of a row, or when
                     // the row grows by more than kLazy (rare, wave-uniform branch)
                     if (__builtin_amdgcn_ballot_w64(lmax > thr[m])) {
-                        const float ymax = group_max4(lmax);
+                        const float ymax = col_max<Q>(lmax);
                         const bool raise = ymax > thr[m];
                         const float dlt = raise ? ymax : 0.f;
                         // a row without a reference has nothing to rescale (and its
                         // first maximum may lie below -128: exp2(-dlt) = inf)
-                        const float alpha = thr[m] == -INFINITY ? 0.f : fast_exp2(-dlt);
+                        const float alpha = thr[m] == kNoRef ? 0.f : fast_exp2(-dlt);
                         mref[m] = raise ? dlt - negm[m] : mref[m];
                         const bool seen = mref[m] != -INFINITY;
                         negm[m] = seen ? -mref[m] : 0.f;
                         negm4[m] = f32x4{negm[m], negm[m], negm[m], negm[m]};
-                        thr[m] = seen ? kLazy : -INFINITY;
-                        if (R > 1) refresh_addends(m);
+                        thr[m] = seen ? kLazy : kNoRef;
+                        if (short_rows) refresh_addends(m);
                         if constexpr (kMfmaSum)
                             lsum[m] *= alpha;
                         else
                             lrow[m] *= alpha;
 #pragma unroll
-                        for (int db = 0; db < C::kDB; ++db) oacc[m][db] *= alpha;
+                        for (int db = 0; db < Ops::kDB; ++db) oacc[m][db] *= alpha;
 #pragma unroll
                         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) y[bi][r] -= dlt;
+                            for (int r = 0; r < kN; ++r) y[bi][r] -= dlt;
                     }
-                    float p[2][4];
+                    float p[2][kN];
 #pragma unroll
                     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) p[bi][r] = fast_exp2(y[bi][r]);
-                    pf[m] = x8{Tr<T>::cvt(p[0][0]), Tr<T>::cvt(p[0][1]), Tr<T>::cvt(p[0][2]),
-                               Tr<T>::cvt(p[0][3]), Tr<T>::cvt(p[1][0]), Tr<T>::cvt(p[1][1]),
-                               Tr<T>::cvt(p[1][2]), Tr<T>::cvt(p[1][3])};
-                    if constexpr (!kMfmaSum) lrow[m] = row_sum8<T>(pf[m], p, lrow[m]);
+                        for (int r = 0; r < kN; ++r) p[bi][r] = fast_exp2(y[bi][r]);
+                    Ops::pack(pf[m], p);
+                    if constexpr (!kMfmaSum)
+#pragma unroll
+                    for (int i = 0; i < Ops::kPF; ++i) lrow[m] = row_sum8<T>(pf[m][i], lrow[m]);
                 }
 
                 // ---- O^T += V^T P^T (and the row sums, ones^T P^T) ----
-                if (!kEarlyV) read_v();
+                if (!kEarlyV && !kMidV) ops.template cols<C::kTileBytes>(kt, vf);
 #pragma unroll
-                for (int db = 0; db < C::kDB; ++db)
+                for (int n_ = 0; n_ < Ops::kF; ++n_)
 #pragma unroll
-                    for (int m = 0; m < QM; ++m) oacc[m][db] = Tr<T>::mma(vf[db], pf[m], oacc[m][db]);
+                    for (int m = 0; m < QM; ++m) Ops::accum(oacc[m], vf[n_], n_, pf[m]);
                 if constexpr (kMfmaSum) {
 #pragma unroll
-                    for (int m = 0; m < QM; ++m) lsum[m] = Tr<T>::mma(ones, pf[m], lsum[m]);
+                    for (int m = 0; m < QM; ++m) Ops::colsum(lsum[m], ones, pf[m]);
                 }
             };
             // Tiles of two full blocks (kind 1, rows of more than two blocks) or
             // of two outer-full blocks (kind 2, short rows) are visited first, by
             // bodies without per-block branches, then (short rows) those with one
             // outer-full block; the order of tiles is free in the online softmax.
-            run_tile_kinds<short_rows>(tiles, fullm, ofullm, tile);
+            // (narrow form: every tile, of four rows, runs the one body)
+            if constexpr (!kNar) run_tile_kinds<short_rows>(tiles, fullm, ofullm, tile);
             while (tiles) {
                 const int tp = __builtin_ctzll(tiles) >> 1;
                 tiles &= tiles - 1;
@@ -448,12 +479,9 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_blocks<D, T, QM, W>())) void na
     // ---- epilogue: normalise, store O (rounded once) and the natural-log LSE ----
 #pragma unroll
     for (int m = 0; m < QM; ++m) {
-        const float l = kMfmaSum ? lsum[m][0] : group_sum4(lrow[m]);
+        const float l = kMfmaSum ? Ops::colsum_of(lsum[m], lane) : col_sum<Q>(lrow[m]);
         if (!qvalid[m]) continue;
-        const float inv = 1.f / l;
-#pragma unroll
-        for (int db = 0; db < C::kDB; ++db)
-            st_x4<T>(og + qoff[m] + db * 16 + grp * 4, oacc[m][db] * inv);
+        Ops::store(og + qoff[m], oacc[m], grp, 1.f / l);
         if (grp == 0) lseg[qoff[m] / D] = (mref[m] + __log2f(l)) * kLn2;
     }
 }
@@ -479,22 +507,78 @@ static int max_row_blocks(const Geo& g, int rank) {
     return (e + 15) / 16;
 }
 
-template <int R, int D, typename T, int QM, int SB, int W = 4>
-static hipError_t launch_fwd_inst(const Geo& g, const void* q, const void* k, const void* v,
+// The narrow form of a two-block tiling (32 queries per wave, four waves): the
+// same workgroup tile and halo, its halo rows held in one 16-key block each, but
+// waves cut along the innermost axis so that a wave needs eight columns of every
+// row; a tile is then four rows of eight keys.  Small inner windows leave most of
+// a 16-key block unused otherwise: with k = 7 a 2 x 2 x 8 wave tile visits
+// 8 x 8 x 16 = 1024 keys per query and a 4 x 4 x 2 one 10 x 10 x 8 = 800.
+// Re-cuts g and returns true where that visits at least a tenth fewer tiles.
+static bool narrow_form(Geo& g, int rank, int nb_max) {
+    const int in = rank - 1;
+    if (g.T[in] + g.k[in] - 1 > 16) return false;  // one block per halo row
+    auto rows = [&](const int* wt) {
+        int r = 1;
+        for (int a = 0; a < in; ++a)
+            r *= std::min(wt[a] + g.k[a] - 1, group_len(g.L[a], g.d[a], 0));
+        return r;
+    };
+    const int tiles = (rows(g.WT) + 1) / 2;  // pairs of 16-key rows
+    int best = 0, bt[kMaxRank] = {1, 1, 1};
+    for (int w = 2; w <= 4 && w + g.k[in] - 1 <= 8; w *= 2) {
+        const int nin = g.T[in] / w;  // waves along the innermost axis
+        if (nin != 2 && nin != 4) continue;
+        for (int s = 0; s < in; ++s) {  // the other split, if any, along outer axis s
+            int t[kMaxRank] = {g.T[0], g.T[1], g.T[2]};
+            t[in] = w;
+            t[s] /= 4 / nin;
+            int slots = 0;
+            for (int a = 0; a < in; ++a) slots += 2 * (t[a] - 1);
+            if (t[s] < 1 || slots > 15) continue;
+            const int nt = (rows(t) + 3) / 4;
+            if (!best || nt < best) {
+                best = nt;
+                for (int a = 0; a < kMaxRank; ++a) bt[a] = t[a];
+            }
+        }
+    }
+    g.tab_rows = (nb_max + 15) & ~15;  // (stages hold at most 16 blocks)
+    if (!best || best * 10 > tiles * 9 || 4 * g.tab_rows * 32 / (g.T[in] / bt[in]) > 8192)
+        return false;
+    auto lg = [](int x) { return 31 - __builtin_clz((unsigned)x); };
+    for (int a = 0; a < kMaxRank; ++a) {
+        g.WT[a] = bt[a];
+        g.WGd[a] = g.T[a] / bt[a];
+        g.lgWT[a] = lg(g.WT[a]);
+        g.lgWGd[a] = lg(g.WGd[a]);
+    }
+    return true;
+}
+
+template <int R, int D, typename T, int Q, int QM, int SB, int W = 4>
+static hipError_t launch_fwd_inst(const Geo& g0, const void* q, const void* k, const void* v,
                                   void* o, float* lse, float scale, hipStream_t stream) {
-    using C = FwdCfg<R, D, T, QM, SB, W>;
-    // The register bound asks for no more workgroups per CU than a CU's
-    // 160 KiB of LDS holds, with double buffers (stages of 16 blocks are used
-    // only when the halo fits in one: single).
-    static_assert(fwd_min_blocks<D, T, QM, W>() * (SB >= 16 ? 1 : 2) * C::kBufBytes <= 160 * 1024,
+    using C = FwdCfg<R, D, T, SB, W>;
+    // The register bound asks for no more workgroups (of W waves, over the CU's
+    // four SIMDs) than its 160 KiB of LDS holds, with double buffers (stages of
+    // 16 blocks are used only when the halo fits in one: single).
+    static_assert(fwd_min_waves<D, T, Q, QM>() * 4 / W * (SB >= 16 ? 1 : 2) * C::kBufBytes <= 160 * 1024,
                   "register bound beyond the LDS occupancy");
-    if (g.WGd[0] * g.WGd[1] * g.WGd[2] != W) return hipErrorInvalidConfiguration;
-    const bool short_rows = R > 1 && max_row_blocks(g, R) <= 2;
-    auto kern = na_fwd_kernel<R, D, T, QM, SB, 0, W>;
+    if (g0.WGd[0] * g0.WGd[1] * g0.WGd[2] != W) return hipErrorInvalidConfiguration;
+    const bool short_rows = R > 1 && max_row_blocks(g0, R) <= 2;
+    auto kern = na_fwd_kernel<R, D, T, Q, QM, SB, 0, W>;
     if constexpr (R > 1)  // (1-D halos have one row: never short)
-        if (short_rows) kern = na_fwd_kernel<R, D, T, QM, SB, 1, W>;
-    const int nst_max = (max_halo_blocks(g, R) + SB - 1) / SB;
-    const size_t lds = (nst_max > 1 ? 2 : 1) * C::kBufBytes;
+        if (short_rows) kern = na_fwd_kernel<R, D, T, Q, QM, SB, 1, W>;
+    const int nb_max = max_halo_blocks(g0, R);
+    size_t lds = (nb_max > SB ? 2 : 1) * C::kBufBytes;
+    Geo g = g0;
+    if constexpr (R > 1 && sizeof(T) == 2 && QM == 2) {
+        if (narrow_form(g, R, nb_max)) {
+            kern = na_fwd_kernel<R, D, T, 32, 1, SB, 2, W>;
+            g.tab_off = (int)lds;
+            lds += (size_t)4 / g.WGd[R - 1] * g.tab_rows * 32;
+        }
+    }
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -510,8 +594,8 @@ template <int R, int D, typename T>
 static hipError_t launch_fwd_qm(const Geo& g, int qm, const void* q, const void* k, const void* v,
                                 void* o, float* lse, float scale, hipStream_t stream) {
     if constexpr (sizeof(T) == 4) {
-        if (qm == 1) return launch_fwd_inst<R, D, T, 1, 2>(g, q, k, v, o, lse, scale, stream);
-        return launch_fwd_inst<R, D, T, 2, 2>(g, q, k, v, o, lse, scale, stream);
+        if (qm == 1) return launch_fwd_inst<R, D, T, 16, 1, 2>(g, q, k, v, o, lse, scale, stream);
+        return launch_fwd_inst<R, D, T, 16, 2, 2>(g, q, k, v, o, lse, scale, stream);
     } else {
         // One block per wave at D = 128: stages of half the keys, so that the
         // four waves per SIMD the registers allow also fit in LDS.
@@ -520,19 +604,19 @@ static hipError_t launch_fwd_qm(const Geo& g, int qm, const void* q, const void*
         if constexpr (R == 1) {
             if (g.WGd[0] == 8) {
                 if (qm == 1)
-                    return launch_fwd_inst<R, D, T, 1, kSB1 * 2, 8>(g, q, k, v, o, lse, scale, stream);
-                return launch_fwd_inst<R, D, T, 2, 8, 8>(g, q, k, v, o, lse, scale, stream);
+                    return launch_fwd_inst<R, D, T, 16, 1, kSB1 * 2, 8>(g, q, k, v, o, lse, scale, stream);
+                return launch_fwd_inst<R, D, T, 16, 2, 8, 8>(g, q, k, v, o, lse, scale, stream);
             }
         }
         // one LDS stage covering the whole halo when it is small and D is 32
         if constexpr (D == 32) {
             if (max_halo_blocks(g, R) <= 16) {
-                if (qm == 1) return launch_fwd_inst<R, D, T, 1, 16>(g, q, k, v, o, lse, scale, stream);
-                return launch_fwd_inst<R, D, T, 2, 16>(g, q, k, v, o, lse, scale, stream);
+                if (qm == 1) return launch_fwd_inst<R, D, T, 16, 1, 16>(g, q, k, v, o, lse, scale, stream);
+                return launch_fwd_inst<R, D, T, 16, 2, 16>(g, q, k, v, o, lse, scale, stream);
             }
         }
-        if (qm == 1) return launch_fwd_inst<R, D, T, 1, kSB1>(g, q, k, v, o, lse, scale, stream);
-        return launch_fwd_inst<R, D, T, 2, 4>(g, q, k, v, o, lse, scale, stream);
+        if (qm == 1) return launch_fwd_inst<R, D, T, 16, 1, kSB1>(g, q, k, v, o, lse, scale, stream);
+        return launch_fwd_inst<R, D, T, 16, 2, 4>(g, q, k, v, o, lse, scale, stream);
     }
 }
 

@@ -61,6 +61,11 @@ struct Box {
         if (R >= 2) oc[0] = row;
     }
 
+    // The same for staging, where blocks past the end stand for the last one.
+    __device__ __forceinline__ int block_first(int b, int& valid) const {
+        return block_token(b < nb ? b : nb - 1, valid);
+    }
+
     // Token (within the (batch, head) slice) of slot 0 of block b, and how many
     // slots of the block hold a token of the box (0 for blocks past the end).
     // Slot j of the block is token + j * g.d[R-1].
@@ -194,6 +199,89 @@ __device__ __forceinline__ void run_tile_kinds(uint64_t& tiles, uint64_t full, u
 }
 
 // ---------------------------------------------------------------------------
+// Outer-axis masks as a matrix product (the narrow form).  Along an axis the
+// box positions a wave needs, counted from the first, fall into three runs: the
+// first nlow are missing from the windows of the wave's later tokens, those from
+// nfirst on (past the first token's window) from the earlier ones', and what lies
+// between belongs to all.  With one slot per position of the outer runs (at most
+// WT - 1 each), a box row's operand has a one in the slots its coordinates fall
+// into, a token's operand kMasked in the slots it misses, and their product is
+// what to add to the pair's score: 0, or at most kMasked.  Slot 15 marks rows that
+// no token of the wave needs.  One 32x32x16 bf16 step per tile (32 cycles of the
+// matrix core) takes the place of two compares per axis, row and lane and a select
+// per score; bf16 because its range makes kMasked exceed any score.
+// ---------------------------------------------------------------------------
+constexpr float kMasked = -9.9692e37f;  // bf16 0xfe96
+
+template <int R>
+struct MaskRows {
+    int lo[kMaxRank], len[kMaxRank], nlow[kMaxRank], nfirst[kMaxRank], slot[kMaxRank];
+
+    __device__ __forceinline__ void init(const Geo& g, const WaveRange<R>& wr, const int* nlow_,
+                                         const int* nfirst_) {
+        int s = 0;
+#pragma unroll
+        for (int a = 0; a < R - 1; ++a) {
+            lo[a] = wr.lo[a];
+            len[a] = wr.rlen[a];
+            nlow[a] = nlow_[a];
+            nfirst[a] = nfirst_[a];
+            slot[a] = s;
+            s += 2 * (g.WT[a] - 1);
+        }
+    }
+
+    // Table `idx` of the workgroup: 16 bf16 slots per box row, the rows one wave
+    // needs them for; rows past the box are marked.
+    __device__ __forceinline__ void write_table(const Geo& g, const Box<R>& box,
+                                                unsigned char* tab, int idx, int lane) const {
+        tab += idx * g.tab_rows * 32;
+        for (int row = lane; row < g.tab_rows; row += kWave) {
+            int oc[kMaxRank], inner0;
+            box.block_coords(row, oc, inner0);
+            unsigned m = row < box.nb ? 0u : 1u << 15;
+#pragma unroll
+            for (int a = 0; a < R - 1; ++a) {
+                const int x = oc[a] - lo[a];
+                if ((unsigned)x >= (unsigned)len[a]) {
+                    m |= 1u << 15;
+                } else {
+                    if (x < nlow[a]) m |= 1u << (slot[a] + x);
+                    if (x >= nfirst[a]) m |= 1u << (slot[a] + g.WT[a] - 1 + x - nfirst[a]);
+                }
+            }
+            st16<i32x4>(tab + row * 32, expand(m, 0x3f80u));
+            st16<i32x4>(tab + row * 32 + 16, expand(m >> 8, 0x3f80u));
+        }
+    }
+
+    // The operand of the token whose windows start at qs[] (box coordinates):
+    // slots 8 grp .. 8 grp + 7.
+    __device__ __forceinline__ i32x4 query_operand(const Geo& g, const int* qs, int grp) const {
+        unsigned m = 1u << 15;
+#pragma unroll
+        for (int a = 0; a < R - 1; ++a) {
+            const int n = g.WT[a] - 1, dq = qs[a] - lo[a];
+            const int miss = min(max(dq, 0), n);                           // first positions missed
+            const int have = min(max(dq + g.k[a] - nfirst[a], 0), n);      // last ones reached
+            m |= ((1u << miss) - 1u) << slot[a];
+            m |= (((1u << n) - 1u) & ~((1u << have) - 1u)) << (slot[a] + n);
+        }
+        return expand(m >> (8 * grp), 0xfe96u);
+    }
+
+  private:
+    // bits 0..7 of m as eight 16-bit values: v where set
+    __device__ __forceinline__ static i32x4 expand(unsigned m, unsigned v) {
+        i32x4 r;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            r[j] = (int)(((m >> (2 * j)) & 1u ? v : 0u) | ((m >> (2 * j + 1)) & 1u ? v << 16 : 0u));
+        return r;
+    }
+};
+
+// ---------------------------------------------------------------------------
 // LDS rows: D elements of T per token, row-major and unpadded, cut into
 // 16-byte segments; segment s of row r is stored at position s ^ swz(r).
 // The swizzle is linear in the low four row bits and was chosen (by an
@@ -211,7 +299,7 @@ struct Rows {
     static constexpr int kVec = 16 / (int)sizeof(T);  // elements per segment
     static_assert(kSegs == 4 || kSegs == 8 || kSegs == 16 || kSegs == 32, "segments per row");
 
-    __device__ __forceinline__ static int swz(int r) {
+    __device__ __forceinline__ static constexpr int swz(int r) {
         constexpr int c0 = kSegs == 4 ? 0 : kSegs == 32 ? 1 : 2;
         constexpr int c1 = kSegs == 4 ? 2 : kSegs == 32 ? 2 : 4;
         constexpr int c2 = kSegs == 4 ? 3 : kSegs == 8 ? 3 : kSegs == 16 ? 9 : 4;
@@ -231,12 +319,21 @@ __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" 
 
 typedef __attribute__((address_space(3))) void lds_void;
 
+// x, with its value hidden from the optimiser.
+__device__ __forceinline__ int opaque(int x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(x));
+#endif
+    return x;
+}
+
 // Stages ROWS token rows into an LDS tile with 16-byte direct-to-LDS loads
 // (no register round trip): wave instruction t writes the tile's 16-byte
 // positions [64 t, 64 t + 64), i.e. 64 / kSegs rows of one 16-row block, and
 // lane l loads the segment that the swizzle puts at position 64 t + l.
-// Tokens missing from the box are replaced by token 0 of the slice (finite
-// data that the masks exclude).  Several tensors with the same rows share one
+// Rows past the end of a box row are replaced by the first row of their block,
+// blocks past the end of the box by its last one (data of the box that the masks
+// exclude).  Several tensors with the same rows share one
 // set of per-lane source offsets.  With BLOCKWISE, when a block takes several
 // instructions, wave w of the W takes the consecutive ones [w * kPerWave,
 // (w + 1) * kPerWave), so that one block decode serves all of a block's
@@ -253,36 +350,55 @@ struct DirectRows {
         return BLOCKWISE && kRowsPerInstr < 16 ? wave * kPerWave + u : wave + W * u;
     }
     static_assert(ROWS % 16 == 0 && kInstr >= 1, "whole blocks per stage");
-    int src[kPerWave];  // element offset (within the slice) of this lane's segment
+    // A block costs its first token (uniform, on the scalar unit); 16-bit types
+    // (slices below 2^32 bytes) load from a scalar base plus a 32-bit lane offset.
+    using Off = std::conditional_t<sizeof(T) == 2, uint32_t, int64_t>;
+    int64_t base[kPerWave];  // the stage's blocks: byte offset within the slice
+    Off cur[kPerWave];       // this lane's segment: byte offset from its block's first token
 
     // Rows of stage-local blocks b0, b0 + 1, ... of the box; tstep is the token
-    // distance between consecutive slots of a block.
-    template <int R>
+    // distance between consecutive slots of a block.  AFRESH forms the lane's part
+    // for each stage again: kernels without registers to spare would spill it in
+    // the tile loop.
+    template <bool AFRESH, int R>
     __device__ __forceinline__ void compute(const Box<R>& box, int b0, int tstep, int wave,
                                             int lane) {
+        if (AFRESH) lane = opaque(lane);
+        const Off rstep = (Off)tstep * (Off)L::kRowBytes;
+        // (round-robin instructions of a wave cover the same rows of their blocks when
+        // W instructions make whole blocks)
+        constexpr int kKinds =
+            (BLOCKWISE && kRowsPerInstr < 16) || W * kRowsPerInstr % 16 != 0 ? kPerWave : 1;
+        int row[kKinds];
+        Off seg0[kKinds], seg[kKinds];
+#pragma unroll
+        for (int u = 0; u < kKinds; ++u) {
+            row[u] = ((instr(wave, u) * kRowsPerInstr) & 15) + lane / L::kSegs;
+            seg0[u] = (Off)(((lane % L::kSegs) ^ L::swz(row[u])) * 16);
+            seg[u] = (Off)row[u] * rstep + seg0[u];
+        }
 #pragma unroll
         for (int u = 0; u < kPerWave; ++u) {
             const int t = instr(wave, u);
-            src[u] = 0;
             if (t < kInstr) {
-                const int row0 = t * kRowsPerInstr;  // first stage-local row (uniform)
                 int valid;
-                const int tok0 = box.block_token(b0 + (row0 >> 4), valid);
-                const int j = (row0 & 15) + lane / L::kSegs;
-                const int seg = (lane % L::kSegs) ^ L::swz(j);
-                const int tok = j < valid ? tok0 + j * tstep : 0;
-                src[u] = tok * D + seg * L::kVec;
+                const int tok0 = box.block_first(b0 + ((t * kRowsPerInstr) >> 4), valid);
+                const int k = kKinds == 1 ? 0 : u;
+                base[u] = (int64_t)tok0 * L::kRowBytes;
+                cur[u] = row[k] < valid ? seg[k] : seg0[k];
             }
         }
     }
 
-    __device__ __forceinline__ void issue(const T* base, unsigned char* tile, int wave) const {
+    __device__ __forceinline__ void issue(const T* slice, unsigned char* tile, int wave) const {
 #pragma unroll
         for (int u = 0; u < kPerWave; ++u) {
             const int t = instr(wave, u);
             if (t < kInstr)
-                __builtin_amdgcn_global_load_lds(static_cast<const void*>(base + src[u]),
-                                                 (lds_void*)(tile + t * 1024), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds(
+                    static_cast<const void*>(reinterpret_cast<const unsigned char*>(slice) +
+                                             base[u] + cur[u]),
+                    (lds_void*)(tile + t * 1024), 16, 0, 0);
         }
     }
 };
@@ -370,6 +486,242 @@ struct ColFrag {
             }
             return v;
         }
+    }
+};
+
+// The same two reads for the 32x32x16 steps (16-bit types, tiles of 32 rows).
+// Row r of a tile is staged row r, or with NARROW the rows of a tile are eight
+// columns (col0 .. col0 + 7) of four consecutive 16-row blocks: staged row
+// 16 (r / 8) + col0 + r % 8.
+// Row fragment st: lane l holds row l % 32, elements st * 16 + 8 (l / 32) .. +7.
+// One offset per lane: fragment st's segment is that of fragment 0 with bits of
+// st flipped in, (2 st + l / 32) ^ swz = 2 st ^ (l / 32 ^ swz), so its offset is
+// formed where it is used (kept apart they would cost three more registers).
+template <typename T, int D>
+struct RowFrag32 {
+    static_assert(sizeof(T) == 2, "16-bit types");
+    using L = Rows<T, D>;
+    static constexpr int kKS = D / 16;
+    int off;
+    template <bool NARROW>
+    __device__ __forceinline__ void init(int lane, int col0) {
+        const int r = lane & 31;
+        off = L::off(NARROW ? (r >> 3) * 16 + col0 + (r & 7) : r, lane >> 5);
+    }
+    __device__ __forceinline__ void read(const unsigned char* tile,
+                                         typename Tr<T>::x8 (&f)[kKS]) const {
+        const int o = opaque(off);  // (not hoisted out of the tile loop)
+#pragma unroll
+        for (int st = 0; st < kKS; ++st)
+            f[st] = __builtin_bit_cast(typename Tr<T>::x8, lds16(tile + (o ^ (st << 5))));
+    }
+};
+
+// Transposed fragment of columns d = db * 32 + l % 32 against the 16 rows of
+// block bi: slot j of lane l is row 4 (l / 32) + j (j < 4) or
+// 8 + 4 (l / 32) + j - 4 (j >= 4) of the block, the rows that lane holds of a
+// 32x32 result tile, so such a tile feeds the next product without a shuffle.
+// (Again one offset per lane: column block db flips segment bits, and the second
+// row of a fragment lies in the next row group, where the swizzle flips bits too.)
+template <typename T, int D, bool NARROW>
+struct ColFrag32 {
+    static_assert(sizeof(T) == 2, "16-bit types");
+    using L = Rows<T, D>;
+    static constexpr int kDB = D / 32;
+    static constexpr int kBlk = (NARROW ? 32 : 16) * L::kRowBytes;  // from bi = 0 to bi = 1
+    static constexpr int kSec = (NARROW ? 16 : 8) * L::kRowBytes;   // to slots 4 .. 7
+    static constexpr int kSecFlip = NARROW ? 0 : L::swz(8) << 4;
+    int off;
+    __device__ __forceinline__ void init(int lane, int col0) {
+        // 16-lane group (2 h + e): rows 4 h + s, columns db * 32 + e * 16 + 4 q .. +3
+        const int h = lane >> 5, e = (lane >> 4) & 1, i = lane & 15;
+        const int r = (NARROW ? col0 : 0) + 4 * h + (i >> 2), q = i & 3;
+        off = L::off(r, (e * 16 + 4 * q) / 8) + (q & 1) * 8;
+    }
+    // Every fragment of the tile, (db, bi) at 2 db + bi, and the wait for them, in
+    // inline-assembly blocks: the compiler takes the transposed read for an access
+    // to any staged row and would wait before it for every direct-to-LDS load in
+    // flight, the next stage's included.
+    // The rows start EXTRA bytes past `tile`.
+    template <int EXTRA>
+    __device__ __forceinline__ void read(const unsigned char* tile,
+                                         typename Tr<T>::x8 (&f)[2 * kDB]) const {
+        static_assert(EXTRA + kBlk + kSec < 65536, "immediate offsets");
+#if defined(__HIP_DEVICE_COMPILE__)
+        typedef const __attribute__((address_space(3))) unsigned char lds_u8;
+        const int o = opaque(off);  // (not hoisted out of the tile loop)
+        if constexpr (kDB == 1) {
+            i32x2 r[4];
+            asm volatile(
+                "ds_read_b64_tr_b16 %0, %4 offset:%6\n\t"
+                "ds_read_b64_tr_b16 %1, %5 offset:%7\n\t"
+                "ds_read_b64_tr_b16 %2, %4 offset:%8\n\t"
+                "ds_read_b64_tr_b16 %3, %5 offset:%9\n\t"
+                "s_waitcnt lgkmcnt(0)"
+                : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+                : "v"((lds_u8*)(tile + o)), "v"((lds_u8*)(tile + (o ^ kSecFlip))), "n"(EXTRA),
+                  "n"(EXTRA + kSec), "n"(EXTRA + kBlk), "n"(EXTRA + kBlk + kSec)
+                : "memory");
+#pragma unroll
+            for (int i = 0; i < 2; ++i) f[i] = cat(r[2 * i], r[2 * i + 1]);
+        } else {
+#pragma unroll
+            for (int db = 0; db < kDB; db += 2) {
+                const int o0 = o ^ (db << 6), o1 = o ^ ((db + 1) << 6);
+                i32x2 r[8];
+                asm volatile(
+                    "ds_read_b64_tr_b16 %0, %8 offset:%12\n\t"
+                    "ds_read_b64_tr_b16 %1, %9 offset:%13\n\t"
+                    "ds_read_b64_tr_b16 %4, %10 offset:%12\n\t"
+                    "ds_read_b64_tr_b16 %5, %11 offset:%13\n\t"
+                    "ds_read_b64_tr_b16 %2, %8 offset:%14\n\t"
+                    "ds_read_b64_tr_b16 %3, %9 offset:%15\n\t"
+                    "ds_read_b64_tr_b16 %6, %10 offset:%14\n\t"
+                    "ds_read_b64_tr_b16 %7, %11 offset:%15\n\t"
+                    "s_waitcnt lgkmcnt(0)"
+                    : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]),
+                      "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+                    : "v"((lds_u8*)(tile + o0)), "v"((lds_u8*)(tile + (o0 ^ kSecFlip))),
+                      "v"((lds_u8*)(tile + o1)), "v"((lds_u8*)(tile + (o1 ^ kSecFlip))),
+                      "n"(EXTRA), "n"(EXTRA + kSec), "n"(EXTRA + kBlk), "n"(EXTRA + kBlk + kSec)
+                    : "memory");
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f[2 * db + i] = cat(r[2 * i], r[2 * i + 1]);
+            }
+        }
+#endif
+    }
+
+  private:
+    __device__ __forceinline__ static typename Tr<T>::x8 cat(i32x2 a, i32x2 b) {
+        return __builtin_bit_cast(typename Tr<T>::x8, i32x4{a[0], a[1], b[0], b[1]});
+    }
+};
+
+// The fragments and products of one tile, 32 staged rows (two 16-row blocks)
+// against a block of Q tokens held in registers, by Q.  kF fragments cover the
+// 32 rows in either orientation.
+//   frag / rows(): the tile's rows as A operand, contraction along D;
+//   cols(): transposed, contraction along the 32 rows;
+//   scores(): s += rows x (register fragments b[]);
+//   accum(): acc[] += cols^T x p, p the tile's values rounded to T.
+template <typename T, int D, int Q, bool NARROW = false>
+struct TileOps;
+
+template <typename T, int D>
+struct TileOps<T, D, 16, false> {
+    using x8 = typename Tr<T>::x8;
+    using Acc = f32x4;
+    static constexpr int kStep = 32, kKS = D / 32, kDB = D / 16, kF = D / 16, kPF = 1;
+    RowFrag<T, D> rf;
+    ColFrag<T, D> cf;
+    int lane;
+    __device__ __forceinline__ void init(int lane_, int = 0) {
+        lane = lane_;
+        rf.init(lane_);
+        cf.init(lane_);
+    }
+    // fragment n = bi * kKS + st
+    __device__ __forceinline__ void rows(const unsigned char* tile, x8 (&f)[kF]) const {
+#pragma unroll
+        for (int n = 0; n < kF; ++n)
+            f[n] = rf.read(tile + (n / kKS) * 16 * Rows<T, D>::kRowBytes, n % kKS);
+    }
+    template <int EXTRA = 0>
+    __device__ __forceinline__ void cols(const unsigned char* tile, x8 (&f)[kF]) const {
+#pragma unroll
+        for (int n = 0; n < kF; ++n) f[n] = cf.read(tile + EXTRA, n, lane);
+    }
+    // product of row fragment n with the register fragments
+    __device__ __forceinline__ static void score(Tile<16>& s, x8 f, int n, const x8 (&b)[kKS]) {
+        s.b[n / kKS] = Tr<T>::mma(f, b[n % kKS], s.b[n / kKS]);
+    }
+    __device__ __forceinline__ static void accum(Acc (&acc)[kDB], x8 f, int n, const x8 (&p)[kPF]) {
+        acc[n] = Tr<T>::mma(f, p[0], acc[n]);
+    }
+    // Column sums of p on the matrix cores: sum += ones^T p, column c's in every
+    // entry (ones_frag: all ones).
+    __device__ __forceinline__ static x8 ones_frag(int) {
+        x8 o;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = (T)1.0f;
+        return o;
+    }
+    __device__ __forceinline__ static void colsum(f32x4& sum, x8 ones, const x8 (&p)[kPF]) {
+        sum = Tr<T>::mma(ones, p[0], sum);
+    }
+    __device__ __forceinline__ static float colsum_of(f32x4 sum, int) { return sum[0]; }
+    __device__ __forceinline__ static void pack(x8 (&pf)[kPF], const float (&p)[2][4]) {
+        pf[0] = x8{Tr<T>::cvt(p[0][0]), Tr<T>::cvt(p[0][1]), Tr<T>::cvt(p[0][2]),
+                   Tr<T>::cvt(p[0][3]), Tr<T>::cvt(p[1][0]), Tr<T>::cvt(p[1][1]),
+                   Tr<T>::cvt(p[1][2]), Tr<T>::cvt(p[1][3])};
+    }
+    // the token row of D elements at p from the column accumulators, scaled
+    __device__ __forceinline__ static void store(T* p, const Acc (&acc)[kDB], int grp, float f) {
+#pragma unroll
+        for (int db = 0; db < kDB; ++db) st_x4<T>(p + db * 16 + grp * 4, acc[db] * f);
+    }
+};
+
+template <typename T, int D, bool NARROW>
+struct TileOps<T, D, 32, NARROW> {
+    using x8 = typename Tr<T>::x8;
+    using Acc = f32x16;
+    static constexpr int kStep = 16, kKS = D / 16, kDB = D / 32, kF = D / 16, kPF = 2;
+    RowFrag32<T, D> rf;
+    ColFrag32<T, D, NARROW> cf;
+    __device__ __forceinline__ void init(int lane, int col0 = 0) {
+        rf.template init<NARROW>(lane, col0);
+        cf.init(lane, col0);
+    }
+    __device__ __forceinline__ void rows(const unsigned char* tile, x8 (&f)[kF]) const {
+        rf.read(tile, f);
+    }
+    // fragment n = db * 2 + bi
+    template <int EXTRA = 0>
+    __device__ __forceinline__ void cols(const unsigned char* tile, x8 (&f)[kF]) const {
+        cf.template read<EXTRA>(tile, f);
+    }
+    __device__ __forceinline__ static void score(Tile<32>& s, x8 f, int n, const x8 (&b)[kKS]) {
+        s.v = Tr<T>::mma(f, b[n], s.v);
+    }
+    __device__ __forceinline__ static void accum(Acc (&acc)[kDB], x8 f, int n, const x8 (&p)[kPF]) {
+        acc[n >> 1] = Tr<T>::mma(f, p[n & 1], acc[n >> 1]);
+    }
+    // Column sums of p with 16x16x32 steps, whose operand B has lane l at column
+    // l % 16 and slots 8 (l / 16): the lanes of columns c and c + 16 fall into one
+    // column there, so the left operand has ones for the even lane groups in its
+    // even rows and for the odd groups in its odd rows, and a lane finds the sum
+    // of its own column in the entry of its group's parity (half the matrix time
+    // of a 32x32x16 step per fragment, and four registers instead of sixteen).
+    __device__ __forceinline__ static x8 ones_frag(int lane) {
+        x8 o;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = (T)(((lane >> 4) & 1) == (lane & 1) ? 1.0f : 0.0f);
+        return o;
+    }
+    __device__ __forceinline__ static void colsum(f32x4& sum, x8 ones, const x8 (&p)[kPF]) {
+        sum = Tr<T>::mma(ones, p[0], sum);
+        sum = Tr<T>::mma(ones, p[1], sum);
+    }
+    __device__ __forceinline__ static float colsum_of(f32x4 sum, int lane) {
+        return (lane >> 4) & 1 ? sum[1] : sum[0];
+    }
+    __device__ __forceinline__ static void pack(x8 (&pf)[kPF], const float (&p)[2][8]) {
+#pragma unroll
+        for (int bi = 0; bi < 2; ++bi)
+            pf[bi] = x8{Tr<T>::cvt(p[bi][0]), Tr<T>::cvt(p[bi][1]), Tr<T>::cvt(p[bi][2]),
+                        Tr<T>::cvt(p[bi][3]), Tr<T>::cvt(p[bi][4]), Tr<T>::cvt(p[bi][5]),
+                        Tr<T>::cvt(p[bi][6]), Tr<T>::cvt(p[bi][7])};
+    }
+    __device__ __forceinline__ static void store(T* p, const Acc (&acc)[kDB], int grp, float f) {
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                st_x4<T>(p + db * 32 + i * 8 + grp * 4,
+                         f32x4{acc[db][4 * i], acc[db][4 * i + 1], acc[db][4 * i + 2],
+                               acc[db][4 * i + 3]} * f);
     }
 };
 
