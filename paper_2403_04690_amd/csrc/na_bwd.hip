@@ -28,35 +28,40 @@ namespace na {
 // ---------------------------------------------------------------------------
 // dQ: query-major, over each query tile's key halo.
 // ---------------------------------------------------------------------------
-template <int R, int D, typename T, int QM, int SB>
+template <int R, int D, typename T, int SB>
 struct DqCfg {
     static constexpr int kThreads = 4 * kWave;
     static constexpr int kKeys = SB * 16;
     static constexpr int kTileBytes = kKeys * Rows<T, D>::kRowBytes;
     static constexpr size_t kBufBytes = 2 * kTileBytes;  // K rows, then V rows
-    static constexpr int kKS = D / 32;
-    static constexpr int kDB = D / 16;
     using Ld = DirectRows<T, D, kKeys, 4, (R > 1)>;
 };
 
+// QM blocks of 16 queries per wave on 16x16x32 steps.
 // SHORT = 1: every halo row holds at most two 16-key blocks (rank >= 2), so
 // the inner-axis mask is a per-lane constant (chosen on the host).
+// SHORT = 2: the narrow form of a QM = 2 tiling, one block of 32 queries on 32x32x16
+// steps with the outer-axis masks from a MaskRows table.
 // braw: the workgroup's index among the dQ-role workgroups.
-template <int R, int D, typename T, int QM, int SB, int SHORT>
+template <int R, int D, typename T, int QM_, int SB, int SHORT>
 __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* smem_raw,
                                         const T* __restrict__ qg, const T* __restrict__ kg,
                                         const T* __restrict__ vg, const T* __restrict__ og,
                                         const T* __restrict__ dog, const float* __restrict__ lseg,
                                         T* __restrict__ dqg, float scale_log2, float scale) {
-    using C = DqCfg<R, D, T, QM, SB>;
+    using C = DqCfg<R, D, T, SB>;
+    constexpr bool kNar = SHORT == 2;
+    constexpr int Q = kNar ? 32 : 16, QM = kNar ? 1 : QM_;
+    using Ops = TileOps<T, D, Q, kNar>;
     using x8 = typename Tr<T>::x8;
     constexpr int kRowB = Rows<T, D>::kRowBytes;
+    constexpr int kN = Tile<Q>::kN;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = uniform((tid >> 6) & (C::kThreads / kWave - 1));  // (bounds the staging loops)
-    const int col = lane & 15;
-    const int grp = lane >> 4;
+    const int col = lane & (Q - 1);
+    const int grp = lane / Q;
 
     const int bid = xcd_remap(braw, g.nwg);
     int bh, gc[kMaxRank], tc[kMaxRank], n[kMaxRank], to[kMaxRank];
@@ -94,6 +99,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
     unravel_pow2<R>(wave, g.lgWGd, wc);
     bool wave_live = true;
     WaveRange<R> wr;
+    MaskRows<R> mrows;  // kNar
 #pragma unroll
     for (int a = 0; a < R; ++a) {
         wo[a] = to[a] + wc[a] * g.WT[a];
@@ -104,17 +110,24 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
         const int sf = win_start(f, n[a], g.k[a], ca), sl = win_start(l, n[a], g.k[a], ca);
         const int ef = win_last(f, n[a], g.k[a], ca), el = win_last(l, n[a], g.k[a], ca);
         wr.set(a, sf - halo.lo[a], el + 1 - halo.lo[a], sl - halo.lo[a], ef + 1 - halo.lo[a]);
+        if (kNar && a < R - 1)
+            mrows.set(a, sf - halo.lo[a], el + 1 - sf, sl - sf, ef + 1 - sf);
+    }
+    const int col0 = kNar ? min(wr.lo[R - 1], 8) : 0;  // narrow form: the wave's first column
+    if constexpr (kNar) {
+        if ((wave & (g.WGd[R - 1] - 1)) == 0 && wave_live)
+            mrows.write_table(g, halo, smem_raw + g.tab_off, wave >> g.lgWGd[R - 1], lane);
     }
 
     int qs[QM][kMaxRank];
     bool qvalid[QM];
     size_t qoff[QM];
-    x8 qf[QM][C::kKS], gf[QM][C::kKS], of[QM][C::kKS];
+    x8 qf[QM][Ops::kKS], gf[QM][Ops::kKS], of[QM][Ops::kKS];
     float lse2[QM], dlt[QM];
 #pragma unroll
     for (int m = 0; m < QM; ++m) {
         int c[kMaxRank];
-        unravel_pow2<R>(m * 16 + col, g.lgWT, c);
+        unravel_pow2<R>(m * Q + col, g.lgWT, c);
         bool ok = wave_live;
         int tok = 0;
 #pragma unroll
@@ -130,42 +143,52 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
 #pragma unroll
         // unconditional: qoff points at a real (clamped) query even for absent
         // slots, whose results are discarded
-        for (int s = 0; s < C::kKS; ++s) {
-            qf[m][s] = ld_x8<T>(qg + qoff[m] + s * 32 + grp * 8);
-            gf[m][s] = ld_x8<T>(dog + qoff[m] + s * 32 + grp * 8);
-            of[m][s] = ld_x8<T>(og + qoff[m] + s * 32 + grp * 8);
+        for (int s = 0; s < Ops::kKS; ++s) {
+            const int e = s * Ops::kStep + grp * 8;
+            qf[m][s] = ld_x8<T>(qg + qoff[m] + e);
+            gf[m][s] = ld_x8<T>(dog + qoff[m] + e);
+            of[m][s] = ld_x8<T>(og + qoff[m] + e);
         }
         lse2[m] = lseg[qoff[m] / D] * kLog2e;
     }
 
-    RowFrag<T, D> rfr;
-    ColFrag<T, D> cfr;
-    rfr.init(lane);
-    cfr.init(lane);
+    Ops ops;
+    ops.init(lane, col0);
+    i32x4 pen{};  // kNar: this lane's mask operand, and its part of a tile's rows
+    unsigned tab_lane = 0;
+    if constexpr (kNar) {
+        unsigned pm = mrows.operand();
+#pragma unroll
+        for (int a = 0; a < R - 1; ++a)
+            pm = mrows.operand(pm, a, qs[0][a], qs[0][a] + g.k[a] - 1);
+        pen = mrows.pack_operand(pm, grp);
+        tab_lane = g.tab_off + (wave >> g.lgWGd[R - 1]) * g.tab_rows * 32 +
+                   (col >> 3) * 32 + grp * 16;
+    }
 
-    f32x4 dqacc[QM][C::kDB];
+    typename Ops::Acc dqacc[QM][Ops::kDB];
 #pragma unroll
     for (int m = 0; m < QM; ++m)
 #pragma unroll
-        for (int db = 0; db < C::kDB; ++db) dqacc[m][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int db = 0; db < Ops::kDB; ++db) dqacc[m][db] = typename Ops::Acc{};
     // Halo rows of at most two 16-key blocks: the inner-axis test of this
     // lane's 4 key slots is fixed, folded with -lse2 into per-slot addends.
     constexpr bool short_rows = SHORT != 0 && R > 1;
     // Score addends folded into the accumulators (not for D = 128 or bf16,
     // as in the forward)
     constexpr bool kFoldAdd = D <= 64 && !std::is_same_v<T, __bf16>;
-    f32x4 ain[QM][2];
+    Tile<Q> ain[QM];
 #pragma unroll
     for (int m = 0; m < QM; ++m)
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < kN; ++r) {
                 const int ib = halo.nbr == 2 ? bi : 0;
-                ain[m][bi][r] =
-                    (unsigned)(ib * 16 + grp * 4 + r - qs[m][R - 1]) < (unsigned)g.k[R - 1]
-                        ? -lse2[m]
-                        : -INFINITY;
+                const int pos = kNar ? col0 + grp * 4 + (r & 3) : ib * 16 + score_row(r, grp);
+                ain[m].set(bi, r, (unsigned)(pos - qs[m][R - 1]) < (unsigned)g.k[R - 1]
+                                      ? -lse2[m]
+                                      : -INFINITY);
             }
 
     const int nst = (halo.nb + SB - 1) / SB;
@@ -174,8 +197,8 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
     for (int m = 0; m < QM; ++m) {
         float part = 0.f;
 #pragma unroll
-        for (int s = 0; s < C::kKS; ++s) part = dot8<T>(of[m][s], gf[m][s], part);
-        dlt[m] = group_sum4(part);
+        for (int s = 0; s < Ops::kKS; ++s) part = dot8<T>(of[m][s], gf[m][s], part);
+        dlt[m] = col_sum<Q>(part);
     }
     wait_vmem();
     __syncthreads();
@@ -188,7 +211,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
 #pragma unroll
     for (int m = 0; m < QM; ++m)
 #pragma unroll
-        for (int st = 0; st < C::kKS; ++st)
+        for (int st = 0; st < Ops::kKS; ++st)
 #pragma unroll
             for (int j = 0; j < 8; ++j) qf[m][st][j] = Tr<T>::cvt((float)qf[m][st][j] * scale_log2);
 
@@ -207,6 +230,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
             const uint64_t fullm = ct.full_bits();
             const uint64_t ofullm = ct.ofull_bits();
             uint64_t tiles = (relm | (relm >> 1)) & 0x5555555555555555ull;
+            if constexpr (kNar) tiles = (tiles | (tiles >> 2)) & 0x1111111111111111ull;
             // The body of one tile (block pair tp), by kind, as in the forward:
             // 0 general; 1 both blocks inside every window of the wave's queries;
             // 2 short rows, both blocks inside every window along the outer axes;
@@ -248,20 +272,57 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
                         const unsigned lim = outer_ok ? (unsigned)g.k[R - 1] : 0u;
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            add[r] = short_rows ? (outer_ok ? ain[m][bi][r] : -INFINITY)
+                            add[r] = short_rows ? (outer_ok ? ain[m].at(bi, r) : -INFINITY)
                                      : (unsigned)(base + r) < lim ? -lse2[m] : -INFINITY;
                     }
                     return add;
                 };
+                const unsigned char* kt = ks + tp * 32 * kRowB;
+                if constexpr (kNar) {
+                    // Every row of the tile is multiplied (rows that no query of the wave
+                    // needs are masked): the inner-axis addends, plus what the outer axes
+                    // mask, seed the scores.
+                    x8 fr[Ops::kF];
+                    ops.rows(kt, fr);
+                    const i32x4 rows = lds16(smem_raw + tab_lane + (s * SB + tp * 2) * 32);
+                    Tile<Q> add, sacc, pacc;
+                    add.v = mma_bf16(rows, pen, ain[0].v);
+                    sacc = kFoldAdd ? add : splat_tile<Q>(0.f);
+#pragma unroll
+                    for (int n_ = 0; n_ < Ops::kF; ++n_) Ops::score(sacc, fr[n_], n_, qf[0]);
+                    x8 fv[Ops::kF];
+                    ops.rows(kt + C::kTileBytes, fv);
+                    pacc = splat_tile<Q>(0.f);
+#pragma unroll
+                    for (int n_ = 0; n_ < Ops::kF; ++n_) Ops::score(pacc, fv[n_], n_, gf[0]);
+                    // K^T for dQ^T += K^T dA^T, read while the products run
+                    x8 fc[Ops::kF];
+                    ops.template cols<0>(kt, fc);
+                    // dA^T = P^T (dP^T - Delta), P = exp2(Y^T)
+                    float ds[2][kN];
+#pragma unroll
+                    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                        for (int r = 0; r < kN; ++r) {
+                            float y = sacc.at(bi, r);
+                            if constexpr (!kFoldAdd) y = fmaf(y, scale_log2, add.at(bi, r));
+                            ds[bi][r] = fast_exp2(y) * (pacc.at(bi, r) - dlt[0]);
+                        }
+                    x8 dsf[Ops::kPF];
+                    Ops::pack(dsf, ds);
+#pragma unroll
+                    for (int n_ = 0; n_ < Ops::kF; ++n_) Ops::accum(dqacc[0], fc[n_], n_, dsf);
+                    return;
+                } else {
                 f32x4 sacc[QM][2], pacc[QM][2];
 #pragma unroll
                 for (int bi = 0; bi < 2; ++bi) {
                     if (rel[bi]) {
                         const int boff = (tp * 2 + bi) * 16 * kRowB;
 #pragma unroll
-                        for (int st = 0; st < C::kKS; ++st) {
-                            const x8 kf = rfr.read(ks + boff, st);
-                            const x8 vf = rfr.read(vs + boff, st);
+                        for (int st = 0; st < Ops::kKS; ++st) {
+                            const x8 kf = ops.rf.read(ks + boff, st);
+                            const x8 vf = ops.rf.read(vs + boff, st);
 #pragma unroll
                             for (int m = 0; m < QM; ++m) {
                                 if (st > 0)
@@ -269,7 +330,8 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
                                 else if (kFoldAdd && !short_rows && full[bi])
                                     sacc[m][bi] = Tr<T>::mma(kf, qf[m][0], nlse4[m]);  // in place
                                 else if (kFoldAdd && short_rows && kOF[bi])
-                                    sacc[m][bi] = Tr<T>::mma(kf, qf[m][0], ain[m][bi]);  // in place
+                                    sacc[m][bi] =
+                                        Tr<T>::mma(kf, qf[m][0], ain[m].b[bi]);  // in place
                                 else
                                     sacc[m][bi] = Tr<T>::mma(kf, qf[m][0],
                                                              kFoldAdd ? score_addend(m, bi)
@@ -289,7 +351,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
                 }
 
                 // dA^T = P^T (dP^T - Delta), P = exp2(Y^T)
-                x8 dsf[QM];
+                x8 dsf[QM][Ops::kPF];
 #pragma unroll
                 for (int m = 0; m < QM; ++m) {
                     float ds[2][4];
@@ -304,21 +366,21 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
 #pragma unroll
                         for (int r = 0; r < 4; ++r) ds[bi][r] = fast_exp2(y[r]) * pacc[m][bi][r];
                     }
-                    dsf[m] = x8{Tr<T>::cvt(ds[0][0]), Tr<T>::cvt(ds[0][1]), Tr<T>::cvt(ds[0][2]),
-                                Tr<T>::cvt(ds[0][3]), Tr<T>::cvt(ds[1][0]), Tr<T>::cvt(ds[1][1]),
-                                Tr<T>::cvt(ds[1][2]), Tr<T>::cvt(ds[1][3])};
+                    Ops::pack(dsf[m], ds);
                 }
 
                 // dQ^T += K^T dA^T (K^T read transposed from the K rows)
 #pragma unroll
-                for (int db = 0; db < C::kDB; ++db) {
-                    const x8 kf = cfr.read(ks + tp * 32 * kRowB, db, lane);
+                for (int db = 0; db < Ops::kDB; ++db) {
+                    const x8 kf = ops.cf.read(kt, db, lane);
 #pragma unroll
-                    for (int m = 0; m < QM; ++m) dqacc[m][db] = Tr<T>::mma(kf, dsf[m], dqacc[m][db]);
+                    for (int m = 0; m < QM; ++m) Ops::accum(dqacc[m], kf, db, dsf[m]);
+                }
                 }
             };
-            // the specialised tiles first (the order of tiles does not matter)
-            run_tile_kinds<short_rows>(tiles, fullm, ofullm, tile);
+            // the specialised tiles first (the order of tiles does not matter; the
+            // narrow form has one body)
+            if constexpr (!kNar) run_tile_kinds<short_rows>(tiles, fullm, ofullm, tile);
             while (tiles) {
                 const int tp = __builtin_ctzll(tiles) >> 1;
                 tiles &= tiles - 1;
@@ -335,9 +397,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
 #pragma unroll
     for (int m = 0; m < QM; ++m) {
         if (!qvalid[m]) continue;
-#pragma unroll
-        for (int db = 0; db < C::kDB; ++db)
-            st_x4<T>(dqg + qoff[m] + db * 16 + grp * 4, dqacc[m][db] * scale);
+        Ops::store(dqg + qoff[m], dqacc[m], grp, scale);
     }
 }
 
@@ -346,7 +406,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
 // ---------------------------------------------------------------------------
 // DIN: -Delta of every query comes from memory (written by a pre-pass), so
 // neither O rows nor a Delta pass are needed.
-template <int R, int D, typename T, int KM, int SB, bool DIN = false>
+template <int R, int D, typename T, int SB, bool DIN = false>
 struct DkvCfg {
     static constexpr int kThreads = 4 * kWave;
     static constexpr int kRows = SB * 16;  // queries per stage
@@ -359,8 +419,6 @@ struct DkvCfg {
     // Q rows, dO rows, [O rows,] then fp32 -lse2 and -Delta per query
     static constexpr size_t kFloatOff = (size_t)kTiles * kTileBytes;
     static constexpr size_t kBufBytes = kFloatOff + 2 * kRows * sizeof(float);
-    static constexpr int kKS = D / 32;
-    static constexpr int kDB = D / 16;
     using Ld = DirectRows<T, D, kRows, 4, (R > 1)>;
 };
 
@@ -376,7 +434,8 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
                                           const float* __restrict__ lseg,
                                           const float* __restrict__ ndg, T* __restrict__ dkg,
                                           T* __restrict__ dvg, float scale_log2, float scale) {
-    using C = DkvCfg<R, D, T, KM, SB, DIN>;
+    using C = DkvCfg<R, D, T, SB, DIN>;
+    using Ops = TileOps<T, D, 16>;
     using x8 = typename Tr<T>::x8;
 
     const int tid = threadIdx.x;
@@ -469,7 +528,7 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
     int kc[KM][kMaxRank];
     bool kvalid[KM];
     size_t koff[KM];
-    x8 kf[KM][C::kKS], vf[KM][C::kKS];
+    x8 kf[KM][Ops::kKS], vf[KM][Ops::kKS];
 #pragma unroll
     for (int m = 0; m < KM; ++m) {
         int c[kMaxRank];
@@ -489,9 +548,9 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
 #pragma unroll
         // unconditional: koff points at a real (clamped) key even for absent
         // slots, whose results are discarded
-        for (int s = 0; s < C::kKS; ++s) {
-            kf[m][s] = ld_x8<T>(kg + koff[m] + s * 32 + grp * 8);
-            vf[m][s] = ld_x8<T>(vg + koff[m] + s * 32 + grp * 8);
+        for (int s = 0; s < Ops::kKS; ++s) {
+            kf[m][s] = ld_x8<T>(kg + koff[m] + s * Ops::kStep + grp * 8);
+            vf[m][s] = ld_x8<T>(vg + koff[m] + s * Ops::kStep + grp * 8);
         }
     }
 
@@ -527,7 +586,6 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
                                     ? 0.f
                                     : -INFINITY;
             }
-
     auto floats = [&](int buf) {
         return reinterpret_cast<float*>(smem_raw + buf * C::kBufBytes + C::kFloatOff);
     };
@@ -572,19 +630,17 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
             if (part == 0) floats(buf)[C::kRows + row] = -acc;  // staged negated: -Delta
         }
     };
-    RowFrag<T, D> rfr;
-    ColFrag<T, D> cfr;
-    rfr.init(lane);
-    cfr.init(lane);
+    Ops ops;
+    ops.init(lane);
     constexpr int kRowB = Rows<T, D>::kRowBytes;
 
-    f32x4 dkacc[KM][C::kDB], dvacc[KM][C::kDB];
+    typename Ops::Acc dkacc[KM][Ops::kDB], dvacc[KM][Ops::kDB];
 #pragma unroll
     for (int m = 0; m < KM; ++m)
 #pragma unroll
-        for (int d = 0; d < C::kDB; ++d) {
-            dkacc[m][d] = f32x4{0.f, 0.f, 0.f, 0.f};
-            dvacc[m][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int d = 0; d < Ops::kDB; ++d) {
+            dkacc[m][d] = typename Ops::Acc{};
+            dvacc[m][d] = typename Ops::Acc{};
         }
 
     const int nst = (ibox.nb + SB - 1) / SB;
@@ -604,7 +660,7 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
 #pragma unroll
     for (int m = 0; m < KM; ++m)
 #pragma unroll
-        for (int st = 0; st < C::kKS; ++st)
+        for (int st = 0; st < Ops::kKS; ++st)
 #pragma unroll
             for (int j = 0; j < 8; ++j) kf[m][st][j] = Tr<T>::cvt((float)kf[m][st][j] * scale_log2);
     if constexpr (!DIN) __syncthreads();  // Delta of the first stage written
@@ -647,6 +703,7 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
                     for (int a = 0; a < R - 1; ++a) boc[bi][a] = ct.outer(j, a);
                 }
 
+                const unsigned char* qt = qs + tp * 32 * kRowB;
                 // -lse2 and -Delta of the 2 x 4 queries this lane holds
                 f32x4 nlse[2], ndl[2];
 #pragma unroll
@@ -688,9 +745,9 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
                     if (rel[bi]) {
                         const int boff = (tp * 2 + bi) * 16 * kRowB;
 #pragma unroll
-                        for (int st = 0; st < C::kKS; ++st) {
-                            const x8 qa = rfr.read(qs + boff, st);
-                            const x8 ga = rfr.read(gs + boff, st);
+                        for (int st = 0; st < Ops::kKS; ++st) {
+                            const x8 qa = ops.rf.read(qs + boff, st);
+                            const x8 ga = ops.rf.read(gs + boff, st);
 #pragma unroll
                             for (int m = 0; m < KM; ++m) {
                                 if (st > 0)
@@ -715,7 +772,7 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
                 }
 
                 // P = exp2(Y), dA = P (dP - Delta)
-                x8 pf[KM], dsf[KM];
+                x8 pf[KM][Ops::kPF], dsf[KM][Ops::kPF];
 #pragma unroll
                 for (int m = 0; m < KM; ++m) {
                     float p[2][4], ds[2][4];
@@ -734,26 +791,22 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
                             ds[bi][r] = pv * pacc[m][bi][r];
                         }
                     }
-                    pf[m] = x8{Tr<T>::cvt(p[0][0]), Tr<T>::cvt(p[0][1]), Tr<T>::cvt(p[0][2]),
-                               Tr<T>::cvt(p[0][3]), Tr<T>::cvt(p[1][0]), Tr<T>::cvt(p[1][1]),
-                               Tr<T>::cvt(p[1][2]), Tr<T>::cvt(p[1][3])};
-                    dsf[m] = x8{Tr<T>::cvt(ds[0][0]), Tr<T>::cvt(ds[0][1]), Tr<T>::cvt(ds[0][2]),
-                                Tr<T>::cvt(ds[0][3]), Tr<T>::cvt(ds[1][0]), Tr<T>::cvt(ds[1][1]),
-                                Tr<T>::cvt(ds[1][2]), Tr<T>::cvt(ds[1][3])};
+                    Ops::pack(pf[m], p);
+                    Ops::pack(dsf[m], ds);
                 }
 
                 // dV^T += dO^T P and dK^T += Q^T dA (transposed reads of the rows)
 #pragma unroll
-                for (int d = 0; d < C::kDB; ++d) {
-                    const x8 ga = cfr.read(gs + tp * 32 * kRowB, d, lane);
-                    const x8 qa = cfr.read(qs + tp * 32 * kRowB, d, lane);
+                for (int d = 0; d < Ops::kDB; ++d) {
+                    const x8 ga = ops.cf.read(gs + tp * 32 * kRowB, d, lane);
+                    const x8 qa = ops.cf.read(qt, d, lane);
 #pragma unroll
                     for (int m = 0; m < KM; ++m) {
-                        dvacc[m][d] = Tr<T>::mma(ga, pf[m], dvacc[m][d]);
-                        dkacc[m][d] = Tr<T>::mma(qa, dsf[m], dkacc[m][d]);
+                        Ops::accum(dvacc[m], ga, d, pf[m]);
+                        Ops::accum(dkacc[m], qa, d, dsf[m]);
                     }
                 }
-                        };
+            };
             // the specialised tiles first (the order of tiles does not matter);
             // 16-bit types at D <= 64 only (the compiler fails on the others)
             if constexpr (sizeof(T) == 2 && D <= 64)
@@ -779,11 +832,8 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
 #pragma unroll
     for (int m = 0; m < KM; ++m) {
         if (!kvalid[m]) continue;
-#pragma unroll
-        for (int d = 0; d < C::kDB; ++d) {
-            st_x4<T>(dkg + koff[m] + d * 16 + grp * 4, dkacc[m][d] * scale);
-            st_x4<T>(dvg + koff[m] + d * 16 + grp * 4, dvacc[m][d]);
-        }
+        Ops::store(dkg + koff[m], dkacc[m], grp, scale);
+        Ops::store(dvg + koff[m], dvacc[m], grp, 1.f);
     }
 }
 
@@ -804,39 +854,34 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
 // registers, and a tighter bound would only spill.  Rank 1 at D = 64 stages
 // 64 queries instead (about 34 KiB), which leaves room for the third wave,
 // and D = 32 stages 128 (about 34 KiB): four waves at rank 1, three above.
-template <int R, int D, typename T, int QM, int ROLE>
+template <int R, int D, typename T, int M, int ROLE>
 constexpr int bwd_min_waves() {
-    if constexpr (ROLE == 2) return sizeof(T) == 2 && D <= 64 ? (QM == 1 ? 5 : 3) : 2;
+    if constexpr (ROLE == 2) return sizeof(T) == 2 && D <= 64 ? (M == 1 ? 5 : 3) : 2;
     if constexpr (ROLE == 1) return R == 1 && D == 64 ? 3 : (D == 32 ? (R == 1 ? 4 : 3) : 2);
     return sizeof(T) == 2 && D <= 64 ? (R == 1 ? 3 : 2) : 1;
 }
 
-template <int R, int D, typename T, int QM, int KM, int SBQ, int SBK, int SHORT, int ROLE>
-__global__ __launch_bounds__(256, (bwd_min_waves<R, D, T, QM, ROLE>())) void na_bwd_kernel(Geo g, int nwk, const T* __restrict__ q,
-                                                     const T* __restrict__ k,
-                                                     const T* __restrict__ v,
-                                                     const T* __restrict__ o,
-                                                     const T* __restrict__ dout,
-                                                     const float* __restrict__ lse,
-                                                     const float* __restrict__ ndelta,
-                                                     T* __restrict__ dq, T* __restrict__ dk,
-                                                     T* __restrict__ dv, float scale_log2,
-                                                     float scale) {
+template <int R, int D, typename T, int M, int SBQ, int SBK, int SHORT, int ROLE>
+__global__ __launch_bounds__(256, (bwd_min_waves<R, D, T, M, ROLE>())) void na_bwd_kernel(
+    Geo g, int nwk, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+    const T* __restrict__ o, const T* __restrict__ dout, const float* __restrict__ lse,
+    const float* __restrict__ ndelta, T* __restrict__ dq, T* __restrict__ dk, T* __restrict__ dv,
+    float scale_log2, float scale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int b = blockIdx.x;
     if constexpr (ROLE == 1) {
-        dkdv_role<R, D, T, KM, SBK, SHORT, true>(g, b, nwk, smem_raw, q, k, v, o, dout, lse,
-                                                 ndelta, dk, dv, scale_log2, scale);
+        dkdv_role<R, D, T, M, SBK, SHORT, true>(g, b, nwk, smem_raw, q, k, v, o, dout, lse,
+                                                   ndelta, dk, dv, scale_log2, scale);
     } else if constexpr (ROLE == 2) {
-        dq_role<R, D, T, QM, SBQ, SHORT>(g, b, smem_raw, q, k, v, o, dout, lse, dq, scale_log2,
-                                         scale);
+        dq_role<R, D, T, M, SBQ, SHORT>(g, b, smem_raw, q, k, v, o, dout, lse, dq, scale_log2,
+                                           scale);
     } else {
         if (b < nwk)
-            dkdv_role<R, D, T, KM, SBK, SHORT, false>(g, b, nwk, smem_raw, q, k, v, o, dout, lse,
-                                                      nullptr, dk, dv, scale_log2, scale);
+            dkdv_role<R, D, T, M, SBK, SHORT, false>(g, b, nwk, smem_raw, q, k, v, o, dout,
+                                                        lse, nullptr, dk, dv, scale_log2, scale);
         else
-            dq_role<R, D, T, QM, SBQ, SHORT>(g, b - nwk, smem_raw, q, k, v, o, dout, lse, dq,
-                                             scale_log2, scale);
+            dq_role<R, D, T, M, SBQ, SHORT>(g, b - nwk, smem_raw, q, k, v, o, dout, lse, dq,
+                                               scale_log2, scale);
     }
 }
 
@@ -918,25 +963,33 @@ __global__ __launch_bounds__(256) void na_delta_kernel(const T* __restrict__ o,
 // launch overwrites it), the dK/dV role reading it (no O rows, no Delta pass,
 // one barrier per stage, stages of SBS blocks), then the dQ role; each role
 // runs at the occupancy its own registers and LDS allow.
-template <int R, int D, typename T, int QM, int KM, int SBQ, int SBK>
-static hipError_t launch_bwd_sb(const Geo& g, bool short_rows, bool split, int hq, int hk,
+template <int R, int D, typename T, int M, int SBQ, int SBK>
+static hipError_t launch_bwd_sb(const Geo& g0, bool short_rows, bool split, int hq, int hk,
                                 const void* q, const void* k, const void* v, const void* o,
                                 const float* lse, const void* dout, void* dq, void* dk, void* dv,
                                 float scale, hipStream_t stream) {
-    const size_t lds_q = (hq > SBQ ? 2 : 1) * DqCfg<R, D, T, QM, SBQ>::kBufBytes;
-    const size_t lds_k = (hk > SBK ? 2 : 1) * DkvCfg<R, D, T, KM, SBK>::kBufBytes;
+    using CQ = DqCfg<R, D, T, SBQ>;
+    using CK = DkvCfg<R, D, T, SBK>;
+    const size_t lds_q = (hq > SBQ ? 2 : 1) * CQ::kBufBytes;
+    const size_t lds_k = (hk > SBK ? 2 : 1) * CK::kBufBytes;
     // No register bound asks for more waves per SIMD (workgroups of four
     // waves per CU) than a CU's 160 KiB of LDS holds, with double buffers
     // (stages of 16 blocks are used only when every box fits in one: single).
     constexpr size_t kCuLds = 160 * 1024;
-    constexpr size_t kLdsQ = (SBQ >= 16 ? 1 : 2) * DqCfg<R, D, T, QM, SBQ>::kBufBytes;
-    constexpr size_t kLdsK = (SBK >= 16 ? 1 : 2) * DkvCfg<R, D, T, KM, SBK>::kBufBytes;
-    static_assert(bwd_min_waves<R, D, T, QM, 0>() * (kLdsQ > kLdsK ? kLdsQ : kLdsK) <= kCuLds,
+    constexpr size_t kLdsQ = (SBQ >= 16 ? 1 : 2) * CQ::kBufBytes;
+    constexpr size_t kLdsK = (SBK >= 16 ? 1 : 2) * CK::kBufBytes;
+    static_assert(bwd_min_waves<R, D, T, M, 0>() * (kLdsQ > kLdsK ? kLdsQ : kLdsK) <= kCuLds,
                   "one-launch register bound beyond the LDS occupancy");
-    static_assert(bwd_min_waves<R, D, T, QM, 2>() * kLdsQ <= kCuLds,
+    static_assert(bwd_min_waves<R, D, T, M, 2>() * (kLdsQ + (R > 1 && M == 2 ? kMaskTableBytes : 0)) <=
+                      kCuLds,
                   "dQ-launch register bound beyond the LDS occupancy");
-    const int nwk = (g.nwg + 7) & ~7;
-    auto launch = [&](auto kern, size_t lds, int grid, const float* nd) -> hipError_t {
+    const int nwk = (g0.nwg + 7) & ~7;
+    // a launch of geometry g, its mask tables (if any) behind `lds` bytes of stages
+    auto launch = [&](auto kern, Geo g, size_t lds, int grid, const float* nd) -> hipError_t {
+        if (g.tab_rows) {
+            g.tab_off = (int)lds;
+            lds += mask_table_bytes(g, R);
+        }
         if (lds > 65536) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -954,19 +1007,23 @@ static hipError_t launch_bwd_sb(const Geo& g, bool short_rows, bool split, int h
         if (split) {
             // query blocks per stage of the dK/dV launch (see bwd_min_waves)
             constexpr int SBS = D == 32 ? 8 : (R == 1 ? 4 : 8);
-            const size_t lds_ks = (hk > SBS ? 2 : 1) * DkvCfg<R, D, T, KM, SBS, true>::kBufBytes;
-            static_assert(bwd_min_waves<R, D, T, QM, 1>() * 2 *
-                                  DkvCfg<R, D, T, KM, SBS, true>::kBufBytes <= kCuLds,
+            const size_t lds_ks = (hk > SBS ? 2 : 1) * DkvCfg<R, D, T, SBS, true>::kBufBytes;
+            static_assert(bwd_min_waves<R, D, T, M, 1>() * 2 *
+                                  DkvCfg<R, D, T, SBS, true>::kBufBytes <= kCuLds,
                           "dK/dV-launch register bound beyond the LDS occupancy");
-            auto kk = na_bwd_kernel<R, D, T, QM, KM, SBQ, SBS, 0, 1>;
-            auto kq = na_bwd_kernel<R, D, T, QM, KM, SBQ, SBK, 0, 2>;
-            if constexpr (R > 1)
+            auto kk = na_bwd_kernel<R, D, T, M, SBQ, SBS, 0, 1>;
+            auto kq = na_bwd_kernel<R, D, T, M, SBQ, SBK, 0, 2>;
+            Geo gq = g0;
+            if constexpr (R > 1) {
                 if (short_rows) {
-                    kk = na_bwd_kernel<R, D, T, QM, KM, SBQ, SBS, 1, 1>;
-                    kq = na_bwd_kernel<R, D, T, QM, KM, SBQ, SBK, 1, 2>;
+                    kk = na_bwd_kernel<R, D, T, M, SBQ, SBS, 1, 1>;
+                    kq = na_bwd_kernel<R, D, T, M, SBQ, SBK, 1, 2>;
                 }
+                if constexpr (M == 2)
+                    if (narrow_form(gq, R, hq)) kq = na_bwd_kernel<R, D, T, M, SBQ, SBK, 2, 2>;
+            }
             float* nd = static_cast<float*>(dq);
-            const int64_t rows = (int64_t)g.BH * g.N;
+            const int64_t rows = (int64_t)g0.BH * g0.N;
             constexpr int kRowsPerBlock = 256 / Rows<T, D>::kSegs;
             const int64_t blocks = std::min<int64_t>((rows + kRowsPerBlock - 1) / kRowsPerBlock,
                                                      int64_t(1) << 18);
@@ -975,19 +1032,19 @@ static hipError_t launch_bwd_sb(const Geo& g, bool short_rows, bool split, int h
                                rows);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
-            e = launch(kk, lds_ks, nwk, nd);
+            e = launch(kk, g0, lds_ks, nwk, nd);
             if (e != hipSuccess) return e;
-            return launch(kq, lds_q, g.nwg, nullptr);
+            return launch(kq, gq, lds_q, g0.nwg, nullptr);
         }
     }
     (void)split;
-    auto kern = na_bwd_kernel<R, D, T, QM, KM, SBQ, SBK, 0, 0>;
+    auto kern = na_bwd_kernel<R, D, T, M, SBQ, SBK, 0, 0>;
     if constexpr (R > 1)  // (1-D boxes have one row: never short)
-        if (short_rows) kern = na_bwd_kernel<R, D, T, QM, KM, SBQ, SBK, 1, 0>;
-    return launch(kern, std::max(lds_q, lds_k), nwk + g.nwg, nullptr);
+        if (short_rows) kern = na_bwd_kernel<R, D, T, M, SBQ, SBK, 1, 0>;
+    return launch(kern, g0, std::max(lds_q, lds_k), nwk + g0.nwg, nullptr);
 }
 
-template <int R, int D, typename T, int QM, int KM>
+template <int R, int D, typename T, int M>
 static hipError_t launch_bwd_inst(const Geo& g, const void* q, const void* k, const void* v,
                                   const void* o, const float* lse, const void* dout, void* dq,
                                   void* dk, void* dv, float scale, hipStream_t stream) {
@@ -1003,21 +1060,21 @@ static hipError_t launch_bwd_inst(const Geo& g, const void* q, const void* k, co
     // D = 32, 16-bit: boxes of up to 16 blocks are staged whole (one stage)
     if constexpr (sizeof(T) == 2 && D == 32) {
         if (hq <= 16 && hk <= 16)
-            return launch_bwd_sb<R, D, T, QM, KM, 16, 16>(g, short_rows, split, hq, hk, q, k, v,
-                                                          o, lse, dout, dq, dk, dv, scale, stream);
+            return launch_bwd_sb<R, D, T, M, 16, 16>(g, short_rows, split, hq, hk, q, k, v, o, lse,
+                                                         dout, dq, dk, dv, scale, stream);
     }
     constexpr int SBQ = sizeof(T) == 4 ? 2 : 4;
     constexpr int SBK = (sizeof(T) == 4 || D == 128) ? 2 : 4;
-    return launch_bwd_sb<R, D, T, QM, KM, SBQ, SBK>(g, short_rows, split, hq, hk, q, k, v, o, lse,
-                                                    dout, dq, dk, dv, scale, stream);
+    return launch_bwd_sb<R, D, T, M, SBQ, SBK>(g, short_rows, split, hq, hk, q, k, v, o, lse, dout,
+                                                   dq, dk, dv, scale, stream);
 }
 
 template <int R, int D, typename T>
 static hipError_t launch_bwd_m(const Geo& g, int m, const void* q, const void* k, const void* v,
                                const void* o, const float* lse, const void* dout, void* dq,
                                void* dk, void* dv, float scale, hipStream_t s) {
-    if (m == 1) return launch_bwd_inst<R, D, T, 1, 1>(g, q, k, v, o, lse, dout, dq, dk, dv, scale, s);
-    return launch_bwd_inst<R, D, T, 2, 2>(g, q, k, v, o, lse, dout, dq, dk, dv, scale, s);
+    if (m == 1) return launch_bwd_inst<R, D, T, 1>(g, q, k, v, o, lse, dout, dq, dk, dv, scale, s);
+    return launch_bwd_inst<R, D, T, 2>(g, q, k, v, o, lse, dout, dq, dk, dv, scale, s);
 }
 
 template <int R, typename T>

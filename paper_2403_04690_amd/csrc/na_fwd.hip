@@ -124,7 +124,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
     unravel_pow2<R>(wave, g.lgWGd, wc);
     bool wave_live = true;
     WaveRange<R> wr;
-    int nlow[kMaxRank], nfirst[kMaxRank];  // narrow form: see MaskRows
+    MaskRows<R> mrows;  // narrow form
 #pragma unroll
     for (int a = 0; a < R; ++a) {
         wo[a] = to[a] + wc[a] * g.WT[a];
@@ -135,13 +135,11 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
         const int sf = win_start(f, n[a], g.k[a], ca), sl = win_start(l, n[a], g.k[a], ca);
         const int ef = win_last(f, n[a], g.k[a], ca), el = win_last(l, n[a], g.k[a], ca);
         wr.set(a, sf - halo.lo[a], el + 1 - halo.lo[a], sl - halo.lo[a], ef + 1 - halo.lo[a]);
-        nlow[a] = sl - sf;
-        nfirst[a] = ef + 1 - sf;
+        if (kNar && a < R - 1)
+            mrows.set(a, sf - halo.lo[a], el + 1 - sf, sl - sf, min(ef, el) + 1 - sf);
     }
     const int col0 = kNar ? min(wr.lo[R - 1], 8) : 0;  // narrow form: the wave's first column
-    MaskRows<R> mrows;
     if constexpr (kNar) {
-        mrows.init(g, wr, nlow, nfirst);
         if ((wave & (g.WGd[R - 1] - 1)) == 0 && wave_live)
             mrows.write_table(g, halo, smem_raw + g.tab_off, wave >> g.lgWGd[R - 1], lane);
     }
@@ -179,7 +177,11 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
     i32x4 pen{};  // narrow form: this lane's mask operand
     unsigned tab_lane = 0;
     if constexpr (kNar) {
-        pen = mrows.query_operand(g, qs[0], grp);
+        unsigned pm = mrows.operand();
+#pragma unroll
+        for (int a = 0; a < R - 1; ++a)
+            pm = mrows.operand(pm, a, qs[0][a], qs[0][a] + g.k[a] - 1);
+        pen = mrows.pack_operand(pm, grp);
         tab_lane = g.tab_off + (wave >> g.lgWGd[R - 1]) * g.tab_rows * 32 + (col >> 3) * 32 +
                    grp * 16;
     }
@@ -507,54 +509,6 @@ static int max_row_blocks(const Geo& g, int rank) {
     return (e + 15) / 16;
 }
 
-// The narrow form of a two-block tiling (32 queries per wave, four waves): the
-// same workgroup tile and halo, its halo rows held in one 16-key block each, but
-// waves cut along the innermost axis so that a wave needs eight columns of every
-// row; a tile is then four rows of eight keys.  Small inner windows leave most of
-// a 16-key block unused otherwise: with k = 7 a 2 x 2 x 8 wave tile visits
-// 8 x 8 x 16 = 1024 keys per query and a 4 x 4 x 2 one 10 x 10 x 8 = 800.
-// Re-cuts g and returns true where that visits at least a tenth fewer tiles.
-static bool narrow_form(Geo& g, int rank, int nb_max) {
-    const int in = rank - 1;
-    if (g.T[in] + g.k[in] - 1 > 16) return false;  // one block per halo row
-    auto rows = [&](const int* wt) {
-        int r = 1;
-        for (int a = 0; a < in; ++a)
-            r *= std::min(wt[a] + g.k[a] - 1, group_len(g.L[a], g.d[a], 0));
-        return r;
-    };
-    const int tiles = (rows(g.WT) + 1) / 2;  // pairs of 16-key rows
-    int best = 0, bt[kMaxRank] = {1, 1, 1};
-    for (int w = 2; w <= 4 && w + g.k[in] - 1 <= 8; w *= 2) {
-        const int nin = g.T[in] / w;  // waves along the innermost axis
-        if (nin != 2 && nin != 4) continue;
-        for (int s = 0; s < in; ++s) {  // the other split, if any, along outer axis s
-            int t[kMaxRank] = {g.T[0], g.T[1], g.T[2]};
-            t[in] = w;
-            t[s] /= 4 / nin;
-            int slots = 0;
-            for (int a = 0; a < in; ++a) slots += 2 * (t[a] - 1);
-            if (t[s] < 1 || slots > 15) continue;
-            const int nt = (rows(t) + 3) / 4;
-            if (!best || nt < best) {
-                best = nt;
-                for (int a = 0; a < kMaxRank; ++a) bt[a] = t[a];
-            }
-        }
-    }
-    g.tab_rows = (nb_max + 15) & ~15;  // (stages hold at most 16 blocks)
-    if (!best || best * 10 > tiles * 9 || 4 * g.tab_rows * 32 / (g.T[in] / bt[in]) > 8192)
-        return false;
-    auto lg = [](int x) { return 31 - __builtin_clz((unsigned)x); };
-    for (int a = 0; a < kMaxRank; ++a) {
-        g.WT[a] = bt[a];
-        g.WGd[a] = g.T[a] / bt[a];
-        g.lgWT[a] = lg(g.WT[a]);
-        g.lgWGd[a] = lg(g.WGd[a]);
-    }
-    return true;
-}
-
 template <int R, int D, typename T, int Q, int QM, int SB, int W = 4>
 static hipError_t launch_fwd_inst(const Geo& g0, const void* q, const void* k, const void* v,
                                   void* o, float* lse, float scale, hipStream_t stream) {
@@ -576,7 +530,7 @@ static hipError_t launch_fwd_inst(const Geo& g0, const void* q, const void* k, c
         if (narrow_form(g, R, nb_max)) {
             kern = na_fwd_kernel<R, D, T, 32, 1, SB, 2, W>;
             g.tab_off = (int)lds;
-            lds += (size_t)4 / g.WGd[R - 1] * g.tab_rows * 32;
+            lds += mask_table_bytes(g, R);
         }
     }
     if (lds > 65536) {

@@ -199,12 +199,12 @@ __device__ __forceinline__ void run_tile_kinds(uint64_t& tiles, uint64_t full, u
 }
 
 // ---------------------------------------------------------------------------
-// Outer-axis masks as a matrix product (the narrow form).  Along an axis the
+// Outer-axis masks as a matrix product (32x32x16 kernels, short rows).  Along an axis the
 // box positions a wave needs, counted from the first, fall into three runs: the
 // first nlow are missing from the windows of the wave's later tokens, those from
 // nfirst on (past the first token's window) from the earlier ones', and what lies
-// between belongs to all.  With one slot per position of the outer runs (at most
-// WT - 1 each), a box row's operand has a one in the slots its coordinates fall
+// between belongs to all.  With one slot per position of the outer runs (15 at most,
+// checked on the host), a box row's operand has a one in the slots its coordinates fall
 // into, a token's operand kMasked in the slots it misses, and their product is
 // what to add to the pair's score: 0, or at most kMasked.  Slot 15 marks rows that
 // no token of the wave needs.  One 32x32x16 bf16 step per tile (32 cycles of the
@@ -217,22 +217,18 @@ template <int R>
 struct MaskRows {
     int lo[kMaxRank], len[kMaxRank], nlow[kMaxRank], nfirst[kMaxRank], slot[kMaxRank];
 
-    __device__ __forceinline__ void init(const Geo& g, const WaveRange<R>& wr, const int* nlow_,
-                                         const int* nfirst_) {
-        int s = 0;
-#pragma unroll
-        for (int a = 0; a < R - 1; ++a) {
-            lo[a] = wr.lo[a];
-            len[a] = wr.rlen[a];
-            nlow[a] = nlow_[a];
-            nfirst[a] = nfirst_[a];
-            slot[a] = s;
-            s += 2 * (g.WT[a] - 1);
-        }
+    // Axis a: the wave needs positions [lo, lo + len) of the box; nlow and nfirst as
+    // above.
+    __device__ __forceinline__ void set(int a, int lo_, int len_, int nlow_, int nfirst_) {
+        lo[a] = lo_;
+        len[a] = len_;
+        nlow[a] = nlow_;
+        nfirst[a] = nfirst_;
+        slot[a] = a == 0 ? 0 : slot[a - 1] + nlow[a - 1] + len[a - 1] - nfirst[a - 1];
     }
 
-    // Table `idx` of the workgroup: 16 bf16 slots per box row, the rows one wave
-    // needs them for; rows past the box are marked.
+    // Table `idx` of the workgroup: 16 bf16 slots per block of the box, as the waves
+    // at one outer position need them; blocks past the box are marked.
     __device__ __forceinline__ void write_table(const Geo& g, const Box<R>& box,
                                                 unsigned char* tab, int idx, int lane) const {
         tab += idx * g.tab_rows * 32;
@@ -247,7 +243,7 @@ struct MaskRows {
                     m |= 1u << 15;
                 } else {
                     if (x < nlow[a]) m |= 1u << (slot[a] + x);
-                    if (x >= nfirst[a]) m |= 1u << (slot[a] + g.WT[a] - 1 + x - nfirst[a]);
+                    if (x >= nfirst[a]) m |= 1u << (slot[a] + nlow[a] + x - nfirst[a]);
                 }
             }
             st16<i32x4>(tab + row * 32, expand(m, 0x3f80u));
@@ -255,18 +251,18 @@ struct MaskRows {
         }
     }
 
-    // The operand of the token whose windows start at qs[] (box coordinates):
-    // slots 8 grp .. 8 grp + 7.
-    __device__ __forceinline__ i32x4 query_operand(const Geo& g, const int* qs, int grp) const {
-        unsigned m = 1u << 15;
-#pragma unroll
-        for (int a = 0; a < R - 1; ++a) {
-            const int n = g.WT[a] - 1, dq = qs[a] - lo[a];
-            const int miss = min(max(dq, 0), n);                           // first positions missed
-            const int have = min(max(dq + g.k[a] - nfirst[a], 0), n);      // last ones reached
-            m |= ((1u << miss) - 1u) << slot[a];
-            m |= (((1u << n) - 1u) & ~((1u << have) - 1u)) << (slot[a] + n);
-        }
+    // Mask operand of a token, slots 8 grp .. 8 grp + 7: start with operand(), then
+    // axis by axis the token's own range [first, last] of box positions.
+    __device__ __forceinline__ static unsigned operand() { return 1u << 15; }
+    __device__ __forceinline__ unsigned operand(unsigned m, int a, int first, int last) const {
+        const int nh = len[a] - nfirst[a];
+        const int miss = min(max(first - lo[a], 0), nlow[a]);           // first positions missed
+        const int have = min(max(last + 1 - lo[a] - nfirst[a], 0), nh);  // last ones reached
+        m |= ((1u << miss) - 1u) << slot[a];
+        m |= (((1u << nh) - 1u) & ~((1u << have) - 1u)) << (slot[a] + nlow[a]);
+        return m;
+    }
+    __device__ __forceinline__ static i32x4 pack_operand(unsigned m, int grp) {
         return expand(m >> (8 * grp), 0xfe96u);
     }
 

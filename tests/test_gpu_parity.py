@@ -710,6 +710,56 @@ def test_every_candidate_tiling_matches_the_oracle(na, ext, ks, ds, cs, D, dtype
          f"{len(bwd_c)} backward tilings, worst max err {worst:.3g}")
 
 
+# The narrow form (two-block tilings whose halo rows fit one 16-key block and whose waves can be
+# cut to eight columns of them): window and tile shapes at its limits, axes as short as the window
+# or shorter than a tile, unequal groups, causal axes, scales of either sign and zero, and keys
+# whose scores would swamp every neighbour's if a mask let them through.
+NARROW_CASES = [
+    # (extents, kernel, dilation, causal, head_dim, dtype, wave tile, waves, scale, swamp)
+    ((9, 13, 21), (7, 7, 7), (1, 1, 1), None, 64, "fp16", (2, 2, 8), (2, 2, 1), None, False),
+    ((7, 14, 30), (7, 7, 7), (1, 2, 3), None, 64, "bf16", (2, 2, 8), (2, 2, 1), None, True),
+    ((11, 9, 16), (5, 3, 7), (1, 1, 2), (True, False, True), 32, "fp16", (2, 2, 8), (2, 2, 1),
+     None, False),
+    ((6, 8, 19), (3, 7, 5), (2, 1, 1), (False, True, False), 128, "bf16", (2, 2, 8), (2, 2, 1),
+     None, True),
+    ((4, 5, 11), (4, 5, 6), (1, 1, 1), None, 64, "fp16", (2, 2, 8), (2, 2, 1), None, False),
+    ((25, 39), (11, 5), (1, 3), None, 128, "fp16", (4, 8, 1), (4, 1, 1), None, False),
+    ((44, 37), (11, 5), (3, 2), (True, False), 64, "bf16", (4, 8, 1), (4, 1, 1), -0.2, True),
+    ((40, 24), (9, 4), (1, 1), (False, True), 32, "bf16", (4, 8, 1), (4, 1, 1), 0.0, False),
+    ((30, 9), (30, 3), (1, 1), None, 64, "fp16", (4, 8, 1), (4, 1, 1), -0.1, False),
+    ((17, 23), (2, 1), (1, 1), None, 64, "fp16", (4, 8, 1), (4, 1, 1), None, False),
+]
+
+
+@pytest.mark.parametrize("ext,ks,ds,cs,D,dtype,wt,wg,scale,swamp", NARROW_CASES)
+def test_narrow_form(na, force, ext, ks, ds, cs, D, dtype, wt, wg, scale, swamp):
+    force(NA_BWD_SPLIT=1)  # (the backward's dQ launch has the form too)
+    q, k, v, g = _inputs((2, 2) + ext + (D,), dtype, 47, 4)
+    if swamp:  # one token in 29 with keys a hundred times the others'
+        k.view(2, 2, -1, D)[:, :, ::29] *= 100
+    t = na.Tiling(2, wt, wg)
+    qd, kd, vd, gd = _dev(q, k, v, g)
+    fq, fk, fv, fg = (_f64(x) for x in (q, k, v, g))
+    sc = 1.0 / math.sqrt(D) if scale is None else scale
+    out, lse = na.forward(qd, kd, vd, ks, ds, scale=sc, causal=cs, tiling=t)
+    ro, rl = oracle.forward(fq, fk, fv, ks, ds, sc, causal=cs)
+    e = [_maxerr(out, ro), _maxerr(lse, rl)]
+    # the backward operator from the oracle's stored results; a score sums D products in fp32,
+    # D roundings at most, each relative to the sum of their absolute values
+    so, sl = torch.from_numpy(ro).to(TDT[dtype]), torch.from_numpy(rl).float()
+    grads = na.backward(qd, kd, vd, *_dev(so, sl), gd, ks, ds, scale=sc, causal=cs, tiling=t)
+    refs = oracle.backward_given(fq, fk, fv, _f64(so), _f64(sl), fg, ks, ds, sc, causal=cs,
+                                 abs_sums=True)
+    e_s = _score_error(dtype, D, fq, fk, ks, ds, abs(sc), cs)
+    e_s = e_s + D * _score_error("bf16", D, fq, fk, ks, ds, abs(sc), cs)
+    terms = [np.abs(a) for a in refs[3:]]  # (the oracle's carry the scale's sign)
+    bound = _operator_bound(dtype, D, int(np.prod(ks)), e_s, refs[:3], terms)
+    worst = [float((np.abs(_f64(x) - r) / b).max()) for x, r, b in zip(grads, refs[:3], bound)]
+    _log(f"narrow {ext} k={ks} d={ds} c={cs} D={D} {dtype} scale {sc:.3g}: max err o/lse = "
+         f"{[f'{x:.3g}' for x in e]}, dq/dk/dv / bound = {[f'{x:.3g}' for x in worst]}")
+    assert max(e) <= TOL[dtype] and max(worst) <= 1.0
+
+
 # Head dim 128 with two query blocks per wave: the heuristic picks it for the forward of large
 # 16-bit problems (at least 1024 workgroups remain); the environment forces it for the
 # backward and the 8-wave 1-D forward too.
