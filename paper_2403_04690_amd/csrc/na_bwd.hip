@@ -34,7 +34,7 @@ struct DqCfg {
     static constexpr int kKeys = SB * 16;
     static constexpr int kTileBytes = kKeys * Rows<T, D>::kRowBytes;
     static constexpr size_t kBufBytes = 2 * kTileBytes;  // K rows, then V rows
-    using Ld = DirectRows<T, D, kKeys, 4, (R > 1)>;
+    using Ld = DirectRows<T, D, kKeys, 4, (R > 1), (R > 1 && sizeof(T) == 2 && D <= 64)>;
 };
 
 // QM blocks of 16 queries per wave on 16x16x32 steps.
@@ -419,7 +419,7 @@ struct DkvCfg {
     // Q rows, dO rows, [O rows,] then fp32 -lse2 and -Delta per query
     static constexpr size_t kFloatOff = (size_t)kTiles * kTileBytes;
     static constexpr size_t kBufBytes = kFloatOff + 2 * kRows * sizeof(float);
-    using Ld = DirectRows<T, D, kRows, 4, (R > 1)>;
+    using Ld = DirectRows<T, D, kRows, 4, (R > 1), (R > 1 && sizeof(T) == 2 && D <= 64)>;
 };
 
 // SHORT = 1: every query-box row holds at most two 16-query blocks (rank >= 2).
@@ -854,8 +854,21 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
 // registers, and a tighter bound would only spill.  Rank 1 at D = 64 stages
 // 64 queries instead (about 34 KiB), which leaves room for the third wave,
 // and D = 32 stages 128 (about 34 KiB): four waves at rank 1, three above.
+// D = 128 (rank 1, one block per wave) stages 32 queries or keys, so that the
+// three waves its registers allow (152-166 VGPRs) fit in LDS: 1-D causal k = 512
+// bf16 training step 275 -> 246 us against the single launch, which holds O rows
+// in LDS too, waits at a second barrier per stage and runs the dQ role at the
+// occupancy of the other.
+// Where the split form exists: 16-bit types at D <= 64, and at D = 128 for rank 1 with
+// one block per wave.
+template <int R, int D, typename T, int M>
+constexpr bool has_split() {
+    return sizeof(T) == 2 && (D <= 64 || (R == 1 && M == 1));
+}
+
 template <int R, int D, typename T, int M, int ROLE>
 constexpr int bwd_min_waves() {
+    if constexpr (D == 128 && ROLE != 0) return has_split<R, D, T, M>() ? 3 : 1;
     if constexpr (ROLE == 2) return sizeof(T) == 2 && D <= 64 ? (M == 1 ? 5 : 3) : 2;
     if constexpr (ROLE == 1) return R == 1 && D == 64 ? 3 : (D == 32 ? (R == 1 ? 4 : 3) : 2);
     return sizeof(T) == 2 && D <= 64 ? (R == 1 ? 3 : 2) : 1;
@@ -984,12 +997,8 @@ static hipError_t launch_bwd_sb(const Geo& g0, bool short_rows, bool split, int 
                       kCuLds,
                   "dQ-launch register bound beyond the LDS occupancy");
     const int nwk = (g0.nwg + 7) & ~7;
-    // a launch of geometry g, its mask tables (if any) behind `lds` bytes of stages
-    auto launch = [&](auto kern, Geo g, size_t lds, int grid, const float* nd) -> hipError_t {
-        if (g.tab_rows) {
-            g.tab_off = (int)lds;
-            lds += mask_table_bytes(g, R);
-        }
+    auto launch = [&](auto kern, const Geo& g, size_t lds, int grid,
+                      const float* nd) -> hipError_t {
         if (lds > 65536) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1003,10 +1012,10 @@ static hipError_t launch_bwd_sb(const Geo& g0, bool short_rows, bool split, int 
                            static_cast<T*>(dk), static_cast<T*>(dv), scale * kLog2e, scale);
         return hipGetLastError();
     };
-    if constexpr (sizeof(T) == 2 && D <= 64) {
+    if constexpr (has_split<R, D, T, M>()) {
         if (split) {
             // query blocks per stage of the dK/dV launch (see bwd_min_waves)
-            constexpr int SBS = D == 32 ? 8 : (R == 1 ? 4 : 8);
+            constexpr int SBS = D == 32 ? 8 : D == 128 ? 2 : (R == 1 ? 4 : 8);
             const size_t lds_ks = (hk > SBS ? 2 : 1) * DkvCfg<R, D, T, SBS, true>::kBufBytes;
             static_assert(bwd_min_waves<R, D, T, M, 1>() * 2 *
                                   DkvCfg<R, D, T, SBS, true>::kBufBytes <= kCuLds,
@@ -1014,13 +1023,18 @@ static hipError_t launch_bwd_sb(const Geo& g0, bool short_rows, bool split, int 
             auto kk = na_bwd_kernel<R, D, T, M, SBQ, SBS, 0, 1>;
             auto kq = na_bwd_kernel<R, D, T, M, SBQ, SBK, 0, 2>;
             Geo gq = g0;
+            size_t lds_tab = 0;  // the narrow form's tables, behind the stages
             if constexpr (R > 1) {
                 if (short_rows) {
                     kk = na_bwd_kernel<R, D, T, M, SBQ, SBS, 1, 1>;
                     kq = na_bwd_kernel<R, D, T, M, SBQ, SBK, 1, 2>;
                 }
                 if constexpr (M == 2)
-                    if (narrow_form(gq, R, hq)) kq = na_bwd_kernel<R, D, T, M, SBQ, SBK, 2, 2>;
+                    if (narrow_form(gq, R, hq)) {
+                        kq = na_bwd_kernel<R, D, T, M, SBQ, SBK, 2, 2>;
+                        gq.tab_off = (int)lds_q;
+                        lds_tab = mask_table_bytes(gq, R);
+                    }
             }
             float* nd = static_cast<float*>(dq);
             const int64_t rows = (int64_t)g0.BH * g0.N;
@@ -1034,7 +1048,7 @@ static hipError_t launch_bwd_sb(const Geo& g0, bool short_rows, bool split, int 
             if (e != hipSuccess) return e;
             e = launch(kk, g0, lds_ks, nwk, nd);
             if (e != hipSuccess) return e;
-            return launch(kq, gq, lds_q, g0.nwg, nullptr);
+            return launch(kq, gq, lds_q + lds_tab, g0.nwg, nullptr);
         }
     }
     (void)split;
@@ -1063,7 +1077,7 @@ static hipError_t launch_bwd_inst(const Geo& g, const void* q, const void* k, co
             return launch_bwd_sb<R, D, T, M, 16, 16>(g, short_rows, split, hq, hk, q, k, v, o, lse,
                                                          dout, dq, dk, dv, scale, stream);
     }
-    constexpr int SBQ = sizeof(T) == 4 ? 2 : 4;
+    constexpr int SBQ = sizeof(T) == 4 || (D == 128 && has_split<R, D, T, M>()) ? 2 : 4;
     constexpr int SBK = (sizeof(T) == 4 || D == 128) ? 2 : 4;
     return launch_bwd_sb<R, D, T, M, SBQ, SBK>(g, short_rows, split, hq, hk, q, k, v, o, lse, dout,
                                                    dq, dk, dv, scale, stream);

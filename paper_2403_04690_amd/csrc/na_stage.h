@@ -280,13 +280,17 @@ struct MaskRows {
 // ---------------------------------------------------------------------------
 // LDS rows: D elements of T per token, row-major and unpadded, cut into
 // 16-byte segments; segment s of row r is stored at position s ^ swz(r).
-// The swizzle is linear in the low four row bits and was chosen (by an
-// exhaustive search over such functions) so that both fragment reads below
-// are free of bank conflicts whether the LDS serves 128 or 256 bytes a cycle:
+// The swizzle is linear in the low four row bits and was chosen so that both
+// fragment reads below are free of bank conflicts:
 //   * 16-byte reads of one segment down 16 consecutive rows (MFMA operands
 //     whose contraction runs along D);
 //   * transposed 8-byte reads of 4 consecutive rows x 2 adjacent segments per
-//     16 lanes (operands whose contraction runs along the tokens).
+//     16 lanes (operands whose contraction runs along the tokens).  The LDS
+//     serves 256 bytes a cycle, lane groups 0 and 2, then 1 and 3 (counted:
+//     with rows r and r + 8 on the same pair of segments a third of all LDS
+//     cycles were conflicts, with those of this swizzle none).  Conflict-free
+//     reads took the dK/dV launch of the 1-D k = 1023 backward from 352 to
+//     336 us and its dQ launch from 258 to 244 us.
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 struct Rows {
@@ -299,7 +303,7 @@ struct Rows {
         constexpr int c0 = kSegs == 4 ? 0 : kSegs == 32 ? 1 : 2;
         constexpr int c1 = kSegs == 4 ? 2 : kSegs == 32 ? 2 : 4;
         constexpr int c2 = kSegs == 4 ? 3 : kSegs == 8 ? 3 : kSegs == 16 ? 9 : 4;
-        constexpr int c3 = kSegs == 32 ? 8 : 1;
+        constexpr int c3 = kSegs >= 16 ? 8 : 2;
         return (-(r & 1) & c0) ^ (-((r >> 1) & 1) & c1) ^ (-((r >> 2) & 1) & c2) ^
                (-((r >> 3) & 1) & c3);
     }
@@ -335,7 +339,7 @@ __device__ __forceinline__ int opaque(int x) {
 // (w + 1) * kPerWave), so that one block decode serves all of a block's
 // instructions (2-D / 3-D boxes, whose decode has divisions); otherwise the
 // waves take the instructions round-robin (measured faster for 1-D boxes).
-template <typename T, int D, int ROWS, int W = 4, bool BLOCKWISE = false>
+template <typename T, int D, int ROWS, int W = 4, bool BLOCKWISE = false, bool UNTRACKED = false>
 struct DirectRows {
     using L = Rows<T, D>;
     static constexpr int kRowsPerInstr = 64 / L::kSegs;
@@ -348,9 +352,11 @@ struct DirectRows {
     static_assert(ROWS % 16 == 0 && kInstr >= 1, "whole blocks per stage");
     // A block costs its first token (uniform, on the scalar unit); 16-bit types
     // (slices below 2^32 bytes) load from a scalar base plus a 32-bit lane offset.
-    using Off = std::conditional_t<sizeof(T) == 2, uint32_t, int64_t>;
-    int64_t base[kPerWave];  // the stage's blocks: byte offset within the slice
-    Off cur[kPerWave];       // this lane's segment: byte offset from its block's first token
+    // Offsets count bytes, fp32 ones elements (32 bits hold either).
+    static constexpr int kUnit = sizeof(T) == 2 ? 1 : 4;
+    static constexpr uint32_t kRowUnits = L::kRowBytes / kUnit;
+    uint32_t base[kPerWave];  // the stage's blocks: offset within the slice
+    uint32_t cur[kPerWave];   // this lane's segment: offset from its block's first token
 
     // Rows of stage-local blocks b0, b0 + 1, ... of the box; tstep is the token
     // distance between consecutive slots of a block.  AFRESH forms the lane's part
@@ -360,18 +366,18 @@ struct DirectRows {
     __device__ __forceinline__ void compute(const Box<R>& box, int b0, int tstep, int wave,
                                             int lane) {
         if (AFRESH) lane = opaque(lane);
-        const Off rstep = (Off)tstep * (Off)L::kRowBytes;
+        const uint32_t rstep = (uint32_t)tstep * kRowUnits;
         // (round-robin instructions of a wave cover the same rows of their blocks when
         // W instructions make whole blocks)
         constexpr int kKinds =
             (BLOCKWISE && kRowsPerInstr < 16) || W * kRowsPerInstr % 16 != 0 ? kPerWave : 1;
         int row[kKinds];
-        Off seg0[kKinds], seg[kKinds];
+        uint32_t seg0[kKinds], seg[kKinds];
 #pragma unroll
         for (int u = 0; u < kKinds; ++u) {
             row[u] = ((instr(wave, u) * kRowsPerInstr) & 15) + lane / L::kSegs;
-            seg0[u] = (Off)(((lane % L::kSegs) ^ L::swz(row[u])) * 16);
-            seg[u] = (Off)row[u] * rstep + seg0[u];
+            seg0[u] = (uint32_t)(((lane % L::kSegs) ^ L::swz(row[u])) * (16 / kUnit));
+            seg[u] = (uint32_t)row[u] * rstep + seg0[u];
         }
 #pragma unroll
         for (int u = 0; u < kPerWave; ++u) {
@@ -380,7 +386,7 @@ struct DirectRows {
                 int valid;
                 const int tok0 = box.block_first(b0 + ((t * kRowsPerInstr) >> 4), valid);
                 const int k = kKinds == 1 ? 0 : u;
-                base[u] = (int64_t)tok0 * L::kRowBytes;
+                base[u] = (uint32_t)tok0 * kRowUnits;
                 cur[u] = row[k] < valid ? seg[k] : seg0[k];
             }
         }
@@ -390,12 +396,39 @@ struct DirectRows {
 #pragma unroll
         for (int u = 0; u < kPerWave; ++u) {
             const int t = instr(wave, u);
-            if (t < kInstr)
-                __builtin_amdgcn_global_load_lds(
-                    static_cast<const void*>(reinterpret_cast<const unsigned char*>(slice) +
-                                             base[u] + cur[u]),
-                    (lds_void*)(tile + t * 1024), 16, 0, 0);
+            if (t >= kInstr) continue;
+            const unsigned char* src =
+                reinterpret_cast<const unsigned char*>(slice) + (size_t)base[u] * kUnit;
+            if constexpr (UNTRACKED)
+                load_lds(src, cur[u], tile + t * 1024);
+            else
+                __builtin_amdgcn_global_load_lds(static_cast<const void*>(src + (size_t)cur[u] * kUnit),
+                                                 (lds_void*)(tile + t * 1024), 16, 0, 0);
         }
+    }
+
+    // 16 bytes per lane from base + off to consecutive LDS positions from dst, in inline
+    // assembly (UNTRACKED): the compiler cannot tell the stage buffers apart and waits,
+    // before a transposed LDS read of the current stage, for the next stage's loads too.
+    // It has no output registers; every wait for it is wait_vmem().  (m0 is reserved: the
+    // compiler sets it right where it needs it, so writing it here disturbs nothing.)
+    // Measured both ways, interleaved, the kernels that name it gain 1 % to 4 % and the
+    // others lose as much: 1-D k = 1023 fp16 forward 176 -> 169 us, 2-D 13 x 13 bf16
+    // backward 185 -> 181 us, but that forward 45.1 -> 48.4 us and 1-D D = 128 backward
+    // 244 -> 249 us.
+    __device__ __forceinline__ static void load_lds(const unsigned char* base, uint32_t off,
+                                                    unsigned char* dst) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        const unsigned m0 = (unsigned)(size_t)(lds_void*)dst;
+        static_assert(kUnit == 1, "16-bit types");
+        asm volatile(
+            "s_mov_b32 m0, %2\n\t"
+            "s_nop 0\n\t"
+            "global_load_lds_dwordx4 %0, %1"
+            :
+            : "v"(off), "s"(base), "s"(m0)
+            : "memory");
+#endif
     }
 };
 
