@@ -412,6 +412,10 @@ struct DirectRows {
     // before a transposed LDS read of the current stage, for the next stage's loads too.
     // It has no output registers; every wait for it is wait_vmem().  (m0 is reserved: the
     // compiler sets it right where it needs it, so writing it here disturbs nothing.)
+    // A vector memory instruction may read a scalar register five wait states after a
+    // vector instruction wrote it (a value read back from a lane: a first lane's, a spilled
+    // one), and one that uses m0 one after its write; the compiler keeps neither distance
+    // inside assembly, so the block does: the move and four idle states.
     // Measured both ways, interleaved, the kernels that name it gain 1 % to 4 % and the
     // others lose as much: 1-D k = 1023 fp16 forward 176 -> 169 us, 2-D 13 x 13 bf16
     // backward 185 -> 181 us, but that forward 45.1 -> 48.4 us and 1-D D = 128 backward
@@ -423,7 +427,7 @@ struct DirectRows {
         static_assert(kUnit == 1, "16-bit types");
         asm volatile(
             "s_mov_b32 m0, %2\n\t"
-            "s_nop 0\n\t"
+            "s_nop 3\n\t"
             "global_load_lds_dwordx4 %0, %1"
             :
             : "v"(off), "s"(base), "s"(m0)
