@@ -971,7 +971,7 @@ __global__ __launch_bounds__(256) void na_delta_kernel(const T* __restrict__ o,
 // all fit in one stage gets a single LDS buffer.
 //
 // One launch runs both roles (dK/dV workgroups first).  The split form, for
-// large 16-bit problems at D <= 64, runs three launches instead: a Delta
+// large 16-bit problems (has_split), runs three launches instead: a Delta
 // pre-pass writing -Delta of every query into dq (scratch until the last
 // launch overwrites it), the dK/dV role reading it (no O rows, no Delta pass,
 // one barrier per stage, stages of SBS blocks), then the dQ role; each role

@@ -426,6 +426,13 @@ SPLIT_CASES = [
     ((257,), (64,), (4,), (True,), 64, "bf16", 1, 1),
     ((1500,), (600,), (2,), None, 64, "fp16", 2, 1),  # the 1-D split of long windows
     ((1500,), (600,), (2,), None, 32, "bf16", 2, 1),
+    # D = 128 at rank 1: one stage and several, a causal window of several stages, and two
+    # blocks per wave, which stays one launch
+    ((19,), (5,), (1,), None, 128, "fp16", 1, 1),
+    ((300,), (13,), (3,), None, 128, "fp16", 1, 1),
+    ((1500,), (600,), (2,), (True,), 128, "bf16", 1, 1),
+    ((257,), (64,), (4,), (True,), 128, "bf16", 1, 0),
+    ((257,), (64,), (4,), None, 128, "fp16", 2, 1),
     ((37, 45), (7, 5), (2, 1), None, 32, "fp16", 2, 1),
     ((33, 31), (13, 13), (2, 2), (True, False), 64, "bf16", 1, 1),
     ((5, 40), (3, 17), (1, 1), None, 32, "fp16", 1, 1),
