@@ -420,19 +420,19 @@ na_status run_forward(int rank, const int64_t* extents, const int32_t* ks, const
     return e == hipSuccess ? NA_OK : NA_ERR_HIP;
 }
 
-// Whether a backward runs as the split form (a Delta pre-pass, then the dK/dV
+// Whether a backward may run as the split form (a Delta pre-pass, then the dK/dV
 // and the dQ workgroups as two launches; 16-bit types at D <= 64, and at
 // D = 128 in 1-D with one block per wave, ignored elsewhere): large 3-D
 // problems with two blocks per wave, whose dK/dV role otherwise holds the dQ
 // role to its own occupancy, and 1-D windows of 512 keys or more, where each
 // launch's smaller working set (Q and dO, or K and V, of the slices in flight)
-// stays in L2 (k = 1023 at D = 64: 650 -> 628 us; causal k = 512 at D = 128,
-// the whole step: 275 -> 247 us; 2-D problems lose 14-47 %).
-// NA_BWD_SPLIT=0|1 forces the choice.
+// stays in L2 (2-D problems lose 14-47 %; the launcher keeps 1-D grids too small
+// to gain as one launch).  NA_BWD_SPLIT=0|1 forces the choice (0, or 2: whatever
+// the grid).
 int bwd_split(int rank, const int32_t* ks, const na_tiling& t) {
     if (const char* env = std::getenv("NA_BWD_SPLIT")) {
         if (env[0] == '0') return 0;
-        if (env[0] == '1') return 1;
+        if (env[0] == '1') return 2;
     }
     if (rank == 3 && t.blocks_per_wave == 2) return 1;
     return rank == 1 && ks[0] >= 512 ? 1 : 0;

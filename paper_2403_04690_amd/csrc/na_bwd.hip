@@ -1070,7 +1070,14 @@ static hipError_t launch_bwd_inst(const Geo& g, const void* q, const void* k, co
     const int hq = box_blocks(eq, R), hk = box_blocks(ek, R);
     // rows of every halo (dQ) and query box (dK/dV) hold at most 2 blocks
     const bool short_rows = R > 1 && (eq[R - 1] + 15) / 16 <= 2 && (ek[R - 1] + 15) / 16 <= 2;
-    const bool split = g.bwd_split != 0;  // chosen on the host with the tiling
+    // The split form of 1-D problems needs a large grid: its two more launches and the
+    // tail of each cost 10 to 20 us.  One launch / split, us: D = 128 at 1024 workgroups
+    // (16384 tokens x 4 heads, k = 600) 116 / 137, at 2048 (8192 x 16, k = 512 causal)
+    // 190 / 187, at 4096 (32768 x 8, k = 512) 403 / 384; D = 64 at 256 (2048 x 8, k = 512
+    // causal) 17 / 27, at 2048 (32768 x 8, k = 1023) 271 / 277, at 4096 (32768 x 16,
+    // k = 1023) 568 / 548; D = 32 at 2048 162 / 169, at 4096 323 / 309.
+    constexpr int kSplitGrid = D == 128 ? 2048 : 4096;
+    const bool split = g.bwd_split == 2 || (g.bwd_split && (R != 1 || g.nwg >= kSplitGrid));
     // D = 32, 16-bit: boxes of up to 16 blocks are staged whole (one stage)
     if constexpr (sizeof(T) == 2 && D == 32) {
         if (hq <= 16 && hk <= 16)

@@ -286,7 +286,7 @@ struct Geo {
     int lgWT[kMaxRank];  // log2 WT (wave tiles are powers of two)
     int lgWGd[kMaxRank]; // log2 WGd
     FastDiv fd_ntiles, fd_ngroups, fd_d[kMaxRank], fd_nt[kMaxRank];
-    int bwd_split;       // backward only: run as the split form (chosen on the host)
+    int bwd_split;       // backward only: split form (0 = no, 1 = on large grids, 2 = always)
     int tab_off, tab_rows;  // narrow form only: LDS offset and rows of each mask table
 };
 
