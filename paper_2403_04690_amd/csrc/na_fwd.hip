@@ -190,9 +190,6 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
     }
 
     // ---- online-softmax state (per lane: its query column) ----
-    // kNoRef: thr before the row has a reference; the narrow form's masked scores
-    // are finite, at most kMasked, and must stay below it.
-    constexpr float kNoRef = kNar ? 0.5f * kMasked : -INFINITY;
     // mref: running reference (base 2, -inf until the row sees a key);
     // negm = -mref (0 while mref = -inf) is the scores' addend and thr the
     // score above which the reference must be raised.
@@ -226,7 +223,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
         mref[m] = -INFINITY;
         negm[m] = 0.f;
         negm4[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-        thr[m] = kNoRef;
+        thr[m] = -INFINITY;
         lsum[m] = f32x4{0.f, 0.f, 0.f, 0.f};
         lrow[m] = 0.f;
 #pragma unroll
@@ -420,12 +417,12 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
                         const float dlt = raise ? ymax : 0.f;
                         // a row without a reference has nothing to rescale (and its
                         // first maximum may lie below -128: exp2(-dlt) = inf)
-                        const float alpha = thr[m] == kNoRef ? 0.f : fast_exp2(-dlt);
+                        const float alpha = thr[m] == -INFINITY ? 0.f : fast_exp2(-dlt);
                         mref[m] = raise ? dlt - negm[m] : mref[m];
                         const bool seen = mref[m] != -INFINITY;
                         negm[m] = seen ? -mref[m] : 0.f;
                         negm4[m] = f32x4{negm[m], negm[m], negm[m], negm[m]};
-                        thr[m] = seen ? kLazy : kNoRef;
+                        thr[m] = seen ? kLazy : -INFINITY;
                         if (short_rows) refresh_addends(m);
                         if constexpr (kMfmaSum)
                             lsum[m] *= alpha;

@@ -204,14 +204,14 @@ __device__ __forceinline__ void run_tile_kinds(uint64_t& tiles, uint64_t full, u
 // first nlow are missing from the windows of the wave's later tokens, those from
 // nfirst on (past the first token's window) from the earlier ones', and what lies
 // between belongs to all.  With one slot per position of the outer runs (15 at most,
-// checked on the host), a box row's operand has a one in the slots its coordinates fall
-// into, a token's operand kMasked in the slots it misses, and their product is
-// what to add to the pair's score: 0, or at most kMasked.  Slot 15 marks rows that
-// no token of the wave needs.  One 32x32x16 bf16 step per tile (32 cycles of the
-// matrix core) takes the place of two compares per axis, row and lane and a select
-// per score; bf16 because its range makes kMasked exceed any score.
+// checked on the host), a box row's operand has kMaskRow in the slots its coordinates
+// fall into, a token's operand kMaskTok in the slots it misses, and their product is
+// what to add to the pair's score: 0, or -inf, to which the product of the two bf16
+// values of largest magnitude overflows (1.1e77).  Slot 15 marks rows that no token of
+// the wave needs.  One 32x32x16 bf16 step per tile (32 cycles of the matrix core) takes
+// the place of two compares per axis, row and lane and a select per score.
 // ---------------------------------------------------------------------------
-constexpr float kMasked = -9.9692e37f;  // bf16 0xfe96
+constexpr unsigned kMaskRow = 0x7f7fu, kMaskTok = 0xff7fu;  // bf16 3.39e38, -3.39e38
 
 template <int R>
 struct MaskRows {
@@ -246,8 +246,8 @@ struct MaskRows {
                     if (x >= nfirst[a]) m |= 1u << (slot[a] + nlow[a] + x - nfirst[a]);
                 }
             }
-            st16<i32x4>(tab + row * 32, expand(m, 0x3f80u));
-            st16<i32x4>(tab + row * 32 + 16, expand(m >> 8, 0x3f80u));
+            st16<i32x4>(tab + row * 32, expand(m, kMaskRow));
+            st16<i32x4>(tab + row * 32 + 16, expand(m >> 8, kMaskRow));
         }
     }
 
@@ -263,7 +263,7 @@ struct MaskRows {
         return m;
     }
     __device__ __forceinline__ static i32x4 pack_operand(unsigned m, int grp) {
-        return expand(m >> (8 * grp), 0xfe96u);
+        return expand(m >> (8 * grp), kMaskTok);
     }
 
   private:

@@ -767,6 +767,62 @@ def test_narrow_form(na, force, ext, ks, ds, cs, D, dtype, wt, wg, scale, swamp)
     assert max(e) <= TOL[dtype] and max(worst) <= 1.0
 
 
+# Masks of the narrow form exclude a key whatever the scores: bf16 scores near the end of the fp32
+# range, rows that lie below every ordinary score and keys outside the windows that lie above.
+HUGE_SCORE_CASES = [
+    # (extents, kernel, causal, head_dim, wave tile, waves)
+    ((9, 13, 21), (7, 7, 7), None, 64, (2, 2, 8), (2, 2, 1)),
+    ((8, 9, 19), (5, 7, 7), (True, False, False), 128, (2, 2, 8), (2, 2, 1)),
+    ((25, 39), (11, 5), None, 64, (4, 8, 1), (4, 1, 1)),
+    ((44, 21), (9, 4), None, 32, (4, 8, 1), (4, 1, 1)),
+]
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("ext,ks,cs,D,wt,wg", HUGE_SCORE_CASES)
+def test_narrow_form_masks_huge_scores(na, force, ext, ks, cs, D, wt, wg, sign):
+    force(NA_BWD_SPLIT=1)
+    t, ds, sc = na.Tiling(2, wt, wg), (1,) * len(ext), float(sign)
+    q, k, v, g = _inputs((1, 2) + ext + (D,), "bf16", 53, 4)
+    # every score between -2^125 and -2^126, each key's its own and 2^111 from the next, which is
+    # far more than their rounding: a row is its largest key's value (the logsumexp's error is
+    # one rounding of the products' sum and one of each conversion of base)
+    rank = torch.randperm(math.prod(ext), generator=torch.Generator().manual_seed(5)).view(ext)
+    q[..., 0], q[..., 1] = 2.0 ** 63, 2.0 ** 56
+    k[..., 0] = -sign * 2.0 ** 62 * (1 + (rank // 128).float() / 128)
+    k[..., 1] = -sign * 2.0 ** 62 * (1 + (rank % 128).float() / 128)
+    out, lse = na.forward(*_dev(q, k, v), ks, ds, scale=sc, causal=cs, tiling=t)
+    ro, rl = oracle.forward(_f64(q), _f64(k), _f64(v), ks, ds, sc, causal=cs)
+    np.testing.assert_allclose(_f64(lse), rl, rtol=2.0 ** -21)
+    assert _maxerr(out, ro) <= TOL["bf16"]
+    # ordinary scores but for one key of 1.5e38, in the middle of the problem: rows that see it
+    # are that key's value, all others as if it were not there
+    q[..., 0], q[..., 1] = 1e19, 1.0
+    k[..., :2] = 0
+    mid = tuple(x // 2 for x in ext)
+    k[(slice(None), slice(None)) + mid + (0,)] = sign * 1.5e19
+    fq, fk, fv, fg = (_f64(x) for x in (q, k, v, g))
+    ro, rl = oracle.forward(fq, fk, fv, ks, ds, sc, causal=cs)
+    far = rl < 1e30
+    assert far.any() and not far.all()
+    out, lse = na.forward(*_dev(q, k, v), ks, ds, scale=sc, causal=cs, tiling=t)
+    eo, el = _maxerr(out, ro), float(np.abs(_f64(lse) - rl)[far].max())
+    # their dQ, from the oracle's stored results (a score of 1e38 has no digits after the point,
+    # so the backward of the others is not compared)
+    so, sl = torch.from_numpy(ro).to(TDT["bf16"]), torch.from_numpy(rl).float()
+    dq = na.backward(*_dev(q, k, v, so, sl, g), ks, ds, scale=sc, causal=cs, tiling=t)[0]
+    ref = oracle.backward_given(fq, fk, fv, _f64(so), _f64(sl), fg, ks, ds, sc, causal=cs,
+                                abs_sums=True)
+    dq, rq, aq = (x[far] for x in (_f64(dq), ref[0], np.abs(ref[3])))
+    # rounding of dA relative to the terms' sum, a score error of D roundings of its products
+    # (at most |s| + 12 sqrt(D)), and the stored gradient's own rounding
+    bound = TOL["bf16"] + (2.0 ** -8 + D * 2.0 ** -24 * 100) * aq + 2.0 ** -8 * np.abs(rq)
+    worst = float((np.abs(dq - rq) / bound).max())
+    _log(f"narrow huge {ext} k={ks} c={cs} D={D} scale {sc}: max err o/lse = {eo:.3g} / {el:.3g}, "
+         f"dq / bound = {worst:.3g}")
+    assert eo <= TOL["bf16"] and el <= TOL["bf16"] and worst <= 1.0
+
+
 # Head dim 128 with two query blocks per wave: the heuristic picks it for the forward of large
 # 16-bit problems (at least 1024 workgroups remain); the environment forces it for the
 # backward and the 8-wave 1-D forward too.
