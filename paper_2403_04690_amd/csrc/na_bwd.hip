@@ -177,7 +177,15 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
     // Score addends folded into the accumulators (not for D = 128 or bf16,
     // as in the forward)
     constexpr bool kFoldAdd = D <= 64 && !std::is_same_v<T, __bf16>;
+    // (narrow form: as in the forward)
     Tile<Q> ain[QM];
+    f32x4 ain4{};
+    if constexpr (kNar && !kFoldAdd)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            ain4[r] = (unsigned)(col0 + grp * 4 + r - qs[0][R - 1]) < (unsigned)g.k[R - 1]
+                          ? -lse2[0]
+                          : -INFINITY;
 #pragma unroll
     for (int m = 0; m < QM; ++m)
 #pragma unroll
@@ -214,6 +222,8 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
         for (int st = 0; st < Ops::kKS; ++st)
 #pragma unroll
             for (int j = 0; j < 8; ++j) qf[m][st][j] = Tr<T>::cvt((float)qf[m][st][j] * scale_log2);
+    float cs = scale_log2;
+    if constexpr (kNar && !kFoldAdd) cs = give_sign<T>(qf[0], scale_log2);
 
     ChunkTests<R, SB> ct;  // this wave's block tests, 64 blocks at a time
     for (int s = 0; s < nst; ++s) {
@@ -285,9 +295,9 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
                     x8 fr[Ops::kF];
                     ops.rows(kt, fr);
                     const i32x4 rows = lds16(smem_raw + tab_lane + (s * SB + tp * 2) * 32);
-                    Tile<Q> add, sacc, pacc;
-                    add.v = mma_bf16(rows, pen, ain[0].v);
-                    sacc = kFoldAdd ? add : splat_tile<Q>(0.f);
+                    Tile<Q> sacc, pacc;
+                    sacc = kFoldAdd ? ain[0] : splat_tile<Q>(0.f);
+                    sacc.v = mma_bf16(rows, pen, sacc.v);
 #pragma unroll
                     for (int n_ = 0; n_ < Ops::kF; ++n_) Ops::score(sacc, fr[n_], n_, qf[0]);
                     x8 fv[Ops::kF];
@@ -305,7 +315,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
 #pragma unroll
                         for (int r = 0; r < kN; ++r) {
                             float y = sacc.at(bi, r);
-                            if constexpr (!kFoldAdd) y = fmaf(y, scale_log2, add.at(bi, r));
+                            if constexpr (!kFoldAdd) y = fmaf(y, cs, ain4[r & 3]);
                             ds[bi][r] = fast_exp2(y) * (pacc.at(bi, r) - dlt[0]);
                         }
                     x8 dsf[Ops::kPF];

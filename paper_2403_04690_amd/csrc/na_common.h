@@ -260,6 +260,19 @@ __device__ __forceinline__ float dot8(typename Tr<T>::x8 a, typename Tr<T>::x8 b
     }
 }
 
+// Moves the sign of a score's scaling c into its operand x (exactly; c = 0 into x = 0) and
+// returns |c| (or 1): scores that are masked with -inf before the scaling then stay -inf.
+template <typename T, int N>
+__device__ __forceinline__ float give_sign(typename Tr<T>::x8 (&x)[N], float c) {
+    if (c > 0.f) return c;
+    const float s = c < 0.f ? -1.f : 0.f;
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[n][j] = Tr<T>::cvt((float)x[n][j] * s);
+    return c < 0.f ? -c : 1.f;
+}
+
 // acc + a b of one bf16 32x32x16 step whatever the kernel's type (mask products).
 __device__ __forceinline__ f32x16 mma_bf16(i32x4 a, i32x4 b, f32x16 acc) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),

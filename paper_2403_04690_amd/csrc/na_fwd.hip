@@ -235,18 +235,32 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
     // -inf where not), refreshed only when the reference moves.  Block bi of
     // a tile has inner block index bi when rows hold two blocks, else 0.
     constexpr bool short_rows = SHORT != 0 && R > 1;
-    // (the narrow form's tiles hold the wave's eight columns of four rows)
+    // (the narrow form's tiles hold the wave's eight columns of four rows, so a lane's
+    // addends repeat: without kFoldAdd four of them serve the tile, and the mask product
+    // seeds the scores.  A second tile for the addends would spill Q at D = 64 and reload
+    // it for every tile: 16 x 64 x 64, 7^3 bf16, 8 heads 225 us so, 134 us now; the
+    // ordinary form takes 182)
     Tile<Q> ain[QM];
+    f32x4 ain4[QM];
     auto refresh_addends = [&](int m) {
+        if constexpr (kNar && !kFoldAdd) {
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int r = 0; r < Tile<Q>::kN; ++r) {
-                const int ib = halo.nbr == 2 ? bi : 0;
-                const int pos = kNar ? col0 + grp * 4 + (r & 3) : ib * 16 + score_row(r, grp);
-                const bool v = (unsigned)(pos - qs[m][R - 1]) < (unsigned)g.k[R - 1];
-                ain[m].set(bi, r, v ? negm[m] : -INFINITY);
+            for (int r = 0; r < 4; ++r) {
+                const bool v = (unsigned)(col0 + grp * 4 + r - qs[m][R - 1]) <
+                               (unsigned)g.k[R - 1];
+                ain4[m][r] = v ? negm[m] : -INFINITY;
             }
+        } else {
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                for (int r = 0; r < Tile<Q>::kN; ++r) {
+                    const int ib = halo.nbr == 2 ? bi : 0;
+                    const int pos = kNar ? col0 + grp * 4 + (r & 3) : ib * 16 + score_row(r, grp);
+                    const bool v = (unsigned)(pos - qs[m][R - 1]) < (unsigned)g.k[R - 1];
+                    ain[m].set(bi, r, v ? negm[m] : -INFINITY);
+                }
+        }
     };
     if (short_rows) {
 #pragma unroll
@@ -266,6 +280,9 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
         for (int st = 0; st < Ops::kKS; ++st)
 #pragma unroll
             for (int j = 0; j < 8; ++j) qf[m][st][j] = Tr<T>::cvt((float)qf[m][st][j] * c);
+    // (the narrow form without it: masked before the scaling)
+    float cs = c;
+    if constexpr (kNar && !kFoldAdd) cs = give_sign<T>(qf[0], c);
 
     ChunkTests<R, SB> ct;  // this wave's block tests, 64 blocks at a time
     for (int s = 0; s < nst; ++s) {
@@ -347,14 +364,14 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
                     }
                     return add;
                 };
-                Tile<Q> sacc[QM], addt[QM];
+                Tile<Q> sacc[QM];
                 if constexpr (kNar) {
-                    // the inner-axis addends, plus what the outer axes mask
+                    // what the outer axes mask (on top of the inner-axis addends)
                     const i32x4 rows = lds16(smem_raw + tab_lane + (s * SB + tp * 2) * 32);
 #pragma unroll
                     for (int m = 0; m < QM; ++m) {
-                        addt[m].v = mma_bf16(rows, pen, ain[m].v);
-                        sacc[m] = kFoldAdd ? addt[m] : splat_tile<Q>(0.f);
+                        sacc[m] = kFoldAdd ? ain[m] : splat_tile<Q>(0.f);
+                        sacc[m].v = mma_bf16(rows, pen, sacc[m].v);
 #pragma unroll
                         for (int n_ = 0; n_ < Ops::kF; ++n_)
                             Ops::score(sacc[m], kf[n_], n_, qf[m]);
@@ -394,14 +411,17 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
 #pragma unroll
                             for (int r = 0; r < kN; ++r) y[bi][r] = sacc[m].at(bi, r);
                     } else {
-                        if constexpr (!kNar)
 #pragma unroll
-                            for (int bi = 0; bi < 2; ++bi) addt[m].b[bi] = score_addend(m, bi);
-#pragma unroll
-                        for (int bi = 0; bi < 2; ++bi)
+                        for (int bi = 0; bi < 2; ++bi) {
+                            f32x4 add;
+                            if constexpr (kNar)
+                                add = ain4[m];
+                            else
+                                add = score_addend(m, bi);
 #pragma unroll
                             for (int r = 0; r < kN; ++r)
-                                y[bi][r] = fmaf(sacc[m].at(bi, r), c, addt[m].at(bi, r));
+                                y[bi][r] = fmaf(sacc[m].at(bi, r), cs, add[r & 3]);
+                        }
                     }
                     // this lane's share of the row; the row maximum exceeds the
                     // threshold exactly when some lane's share does
