@@ -25,6 +25,13 @@
 
 namespace na {
 
+// Addressing of the stage loads of a kernel with M blocks per wave (see Addr).
+template <int R, int D, typename T, int M>
+constexpr Addr bwd_addr() {
+    if (sizeof(T) != 2 || (R == 3 && D == 128)) return Addr::kByBlock;
+    return R == 2 && M == 1 && D <= 64 ? Addr::kUntracked : Addr::kByLane;
+}
+
 // ---------------------------------------------------------------------------
 // dQ: query-major, over each query tile's key halo.
 // ---------------------------------------------------------------------------
@@ -34,7 +41,8 @@ struct DqCfg {
     static constexpr int kKeys = SB * 16;
     static constexpr int kTileBytes = kKeys * Rows<T, D>::kRowBytes;
     static constexpr size_t kBufBytes = 2 * kTileBytes;  // K rows, then V rows
-    using Ld = DirectRows<T, D, kKeys, 4, (R > 1), (R > 1 && sizeof(T) == 2 && D <= 64)>;
+    template <int M>
+    using Ld = DirectRows<T, D, kKeys, 4, (R > 1), bwd_addr<R, D, T, M>()>;
 };
 
 // QM blocks of 16 queries per wave on 16x16x32 steps.
@@ -86,7 +94,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
     // The first stage is issued as soon as the halo is known, so that its
     // loads are in flight during the per-wave and per-lane set-up below.
     const int tstep = g.d[R - 1];
-    typename C::Ld ld;
+    typename C::template Ld<QM_> ld;
     auto issue_stage = [&](int s, int buf) {
         ld.template compute<false>(halo, s * SB, tstep, wave, lane);
         unsigned char* tile = smem_raw + buf * C::kBufBytes;
@@ -429,7 +437,8 @@ struct DkvCfg {
     // Q rows, dO rows, [O rows,] then fp32 -lse2 and -Delta per query
     static constexpr size_t kFloatOff = (size_t)kTiles * kTileBytes;
     static constexpr size_t kBufBytes = kFloatOff + 2 * kRows * sizeof(float);
-    using Ld = DirectRows<T, D, kRows, 4, (R > 1), (R > 1 && sizeof(T) == 2 && D <= 64)>;
+    template <int M>
+    using Ld = DirectRows<T, D, kRows, 4, (R > 1), bwd_addr<R, D, T, M>()>;
 };
 
 // SHORT = 1: every query-box row holds at most two 16-query blocks (rank >= 2).
@@ -480,7 +489,7 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
     const float* nb_ = DIN ? ndg + (size_t)bh * g.N : nullptr;
 
     const int tstep = g.d[R - 1];
-    typename C::Ld ld;
+    typename C::template Ld<KM> ld;
     using L = Rows<T, D>;
     // the stage's per-query values as loaded (row tid of the stage), and
     // whether the row holds a query; combined only where they are stored

@@ -50,9 +50,7 @@ struct FwdCfg {
     static constexpr int kKeys = SB * 16;  // keys per stage
     static constexpr int kTileBytes = kKeys * Rows<T, D>::kRowBytes;
     static constexpr size_t kBufBytes = 2 * kTileBytes;  // K rows, then V rows
-    // (UNT: see DirectRows)
-    template <bool UNT>
-    using Ld = DirectRows<T, D, kKeys, W, (R > 1), UNT>;
+    using Ld = DirectRows<T, D, kKeys, W, (R > 1)>;
     static_assert(SB % 2 == 0 && SB <= 32, "stage blocks are tested by one lane each");
 };
 
@@ -112,8 +110,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
     // ---- staging: K and V rows straight to LDS, one address set for both ----
     // The first stage is issued as soon as the halo is known, so that its
     // loads are in flight during the per-wave and per-lane set-up below.
-    constexpr bool kUntracked = sizeof(T) == 2 && D <= 64 && (kNar || (R == 1 && QM == 2));
-    typename C::template Ld<kUntracked> ld;
+    typename C::Ld ld;
     auto issue_stage = [&](int s, int buf) {
         ld.template compute<kNar>(halo, s * SB, tstep, wave, lane);
         unsigned char* tile = smem_raw + buf * C::kBufBytes;

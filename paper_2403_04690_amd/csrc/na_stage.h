@@ -339,7 +339,21 @@ __device__ __forceinline__ int opaque(int x) {
 // (w + 1) * kPerWave), so that one block decode serves all of a block's
 // instructions (2-D / 3-D boxes, whose decode has divisions); otherwise the
 // waves take the instructions round-robin (measured faster for 1-D boxes).
-template <typename T, int D, int ROWS, int W = 4, bool BLOCKWISE = false, bool UNTRACKED = false>
+// How a load is addressed:
+//   kByLane   scalar slice base + 32-bit lane offset (16-bit types, whose slices are
+//             below 2^32 bytes): one base register pair for every load;
+//   kByBlock  scalar base per block + lane offset: no vector add per load, but a
+//             register pair each.  fp32, whose lane offsets may exceed 32 bits, and the
+//             3-D backward at D = 128, measured by block / by lane 16 x 64 x 64, 7^3
+//             1664 / 1735 us, 8 x 96 x 96, 5 x 7 x 7 1200 / 1295.  Elsewhere by lane is the
+//             faster or within 1 %: 1-D k = 255 causal bf16 D = 64 forward 23.7 / 22.8,
+//             3-D 9 x 9 x 5 bf16 D = 64 forward 191 / 186, 2-D 128 x 128 k = 13 d = 2 bf16
+//             D = 32 backward 103.4 / 97.6;
+//   kUntracked  as kByLane, in inline assembly (load_lds below).
+enum class Addr { kByLane, kByBlock, kUntracked };
+
+template <typename T, int D, int ROWS, int W = 4, bool BLOCKWISE = false,
+          Addr ADDR = (sizeof(T) == 2 ? Addr::kByLane : Addr::kByBlock)>
 struct DirectRows {
     using L = Rows<T, D>;
     static constexpr int kRowsPerInstr = 64 / L::kSegs;
@@ -350,13 +364,13 @@ struct DirectRows {
         return BLOCKWISE && kRowsPerInstr < 16 ? wave * kPerWave + u : wave + W * u;
     }
     static_assert(ROWS % 16 == 0 && kInstr >= 1, "whole blocks per stage");
-    // A block costs its first token (uniform, on the scalar unit); 16-bit types
-    // (slices below 2^32 bytes) load from a scalar base plus a 32-bit lane offset.
+    // A block costs its first token (uniform, on the scalar unit).
     // Offsets count bytes, fp32 ones elements (32 bits hold either).
     static constexpr int kUnit = sizeof(T) == 2 ? 1 : 4;
     static constexpr uint32_t kRowUnits = L::kRowBytes / kUnit;
-    uint32_t base[kPerWave];  // the stage's blocks: offset within the slice
-    uint32_t cur[kPerWave];   // this lane's segment: offset from its block's first token
+    static_assert(ADDR == Addr::kByBlock || sizeof(T) == 2, "32-bit byte offsets");
+    uint32_t base[kPerWave];  // kByBlock: the stage's blocks' first tokens within the slice
+    uint32_t cur[kPerWave];   // this lane's segment, from there; else within the slice
 
     // Rows of stage-local blocks b0, b0 + 1, ... of the box; tstep is the token
     // distance between consecutive slots of a block.  AFRESH forms the lane's part
@@ -388,6 +402,7 @@ struct DirectRows {
                 const int k = kKinds == 1 ? 0 : u;
                 base[u] = (uint32_t)tok0 * kRowUnits;
                 cur[u] = row[k] < valid ? seg[k] : seg0[k];
+                if (ADDR != Addr::kByBlock) cur[u] += base[u];
             }
         }
     }
@@ -397,9 +412,9 @@ struct DirectRows {
         for (int u = 0; u < kPerWave; ++u) {
             const int t = instr(wave, u);
             if (t >= kInstr) continue;
-            const unsigned char* src =
-                reinterpret_cast<const unsigned char*>(slice) + (size_t)base[u] * kUnit;
-            if constexpr (UNTRACKED)
+            const unsigned char* src = reinterpret_cast<const unsigned char*>(slice);
+            if (ADDR == Addr::kByBlock) src += (size_t)base[u] * kUnit;
+            if constexpr (ADDR == Addr::kUntracked)
                 load_lds(src, cur[u], tile + t * 1024);
             else
                 __builtin_amdgcn_global_load_lds(static_cast<const void*>(src + (size_t)cur[u] * kUnit),
@@ -408,7 +423,7 @@ struct DirectRows {
     }
 
     // 16 bytes per lane from base + off to consecutive LDS positions from dst, in inline
-    // assembly (UNTRACKED): the compiler cannot tell the stage buffers apart and waits,
+    // assembly: the compiler cannot tell the stage buffers apart and waits,
     // before a transposed LDS read of the current stage, for the next stage's loads too.
     // It has no output registers; every wait for it is wait_vmem().  (m0 is reserved: the
     // compiler sets it right where it needs it, so writing it here disturbs nothing.)
@@ -416,10 +431,11 @@ struct DirectRows {
     // vector instruction wrote it (a value read back from a lane: a first lane's, a spilled
     // one), and one that uses m0 one after its write; the compiler keeps neither distance
     // inside assembly, so the block does: the move and four idle states.
-    // Measured both ways, interleaved, the kernels that name it gain 1 % to 4 % and the
-    // others lose as much: 1-D k = 1023 fp16 forward 176 -> 169 us, 2-D 13 x 13 bf16
-    // backward 185 -> 181 us, but that forward 45.1 -> 48.4 us and 1-D D = 128 backward
-    // 244 -> 249 us.
+    // Used by the 2-D backwards of one block per wave at D <= 64, tracked / untracked, us:
+    // 56 x 56 k = 7 D = 32 fp16, 128 slices 61.6 / 59.7, 128 x 128 k = 13 d = 2 D = 64 fp16
+    // 159.2 / 156.6, 96 x 96 k = 21 d = 2 D = 64 bf16 104.9 / 102.2 (56 x 56 k = 7 D = 64
+    // bf16 loses, 40.9 / 41.6).  Elsewhere it gains nothing or loses: 1-D k = 1023 forward
+    // fp16 166 / 166, bf16 166 / 170, 3-D 7^3 backward bf16 565 / 582.
     __device__ __forceinline__ static void load_lds(const unsigned char* base, uint32_t off,
                                                     unsigned char* dst) {
 #if defined(__HIP_DEVICE_COMPILE__)
