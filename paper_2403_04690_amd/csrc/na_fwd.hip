@@ -136,7 +136,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
         const int ef = win_last(f, n[a], g.k[a], ca), el = win_last(l, n[a], g.k[a], ca);
         wr.set(a, sf - halo.lo[a], el + 1 - halo.lo[a], sl - halo.lo[a], ef + 1 - halo.lo[a]);
         if (kNar && a < R - 1)
-            mrows.set(a, sf - halo.lo[a], el + 1 - sf, sl - sf, min(ef, el) + 1 - sf);
+            mrows.set(a, sf - halo.lo[a], el + 1 - sf, sl - sf, ef + 1 - sf);
     }
     const int col0 = kNar ? min(wr.lo[R - 1], 8) : 0;  // narrow form: the wave's first column
     if constexpr (kNar) {
@@ -506,18 +506,6 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
 }
 
 // ---- host-side launch ----
-// Largest number of 16-key blocks in any workgroup's halo (interior tiles).
-static int max_halo_blocks(const Geo& g, int rank) {
-    int nb = 1;
-    for (int a = 0; a < rank; ++a) {
-        const int n0 = group_len(g.L[a], g.d[a], 0);
-        int e = std::min(g.T[a], n0) + g.k[a] - 1;
-        e = std::min(e, n0);
-        nb *= (a == rank - 1) ? (e + 15) / 16 : e;
-    }
-    return nb;
-}
-
 // Largest number of 16-key blocks in one halo row (interior tiles).
 static int max_row_blocks(const Geo& g, int rank) {
     const int a = rank - 1;

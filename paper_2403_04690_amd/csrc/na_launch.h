@@ -20,6 +20,18 @@ hipError_t launch_backward(const Geo& g, int rank, int D, int dtype, int m, cons
                            const void* dout, void* dq, void* dk, void* dv, float scale,
                            hipStream_t s);
 
+// Largest number of 16-key blocks in any workgroup's halo (interior tiles).
+inline int max_halo_blocks(const Geo& g, int rank) {
+    int nb = 1;
+    for (int a = 0; a < rank; ++a) {
+        const int n0 = group_len(g.L[a], g.d[a], 0);
+        int e = std::min(g.T[a], n0) + g.k[a] - 1;
+        e = std::min(e, n0);
+        nb *= (a == rank - 1) ? (e + 15) / 16 : e;
+    }
+    return nb;
+}
+
 // LDS of the mask tables (MaskRows): one per outer wave position of the workgroup,
 // a row of 32 bytes per 16-token block of the box, rounded to whole stages (of at
 // most 16 blocks).  Larger tables are not used.

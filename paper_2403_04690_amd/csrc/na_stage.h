@@ -219,12 +219,28 @@ struct MaskRows {
 
     // Axis a: the wave needs positions [lo, lo + len) of the box; nlow and nfirst as
     // above.
-    __device__ __forceinline__ void set(int a, int lo_, int len_, int nlow_, int nfirst_) {
+    NA_HD void set(int a, int lo_, int len_, int nlow_, int nfirst_) {
         lo[a] = lo_;
         len[a] = len_;
         nlow[a] = nlow_;
         nfirst[a] = nfirst_;
         slot[a] = a == 0 ? 0 : slot[a - 1] + nlow[a - 1] + len[a - 1] - nfirst[a - 1];
+    }
+
+    // Slots of the box row at outer coordinates oc (relative to the box).
+    NA_HD unsigned row_slots(const int* oc) const {
+        unsigned m = 0;
+#pragma unroll
+        for (int a = 0; a < R - 1; ++a) {
+            const int x = oc[a] - lo[a];
+            if ((unsigned)x >= (unsigned)len[a]) {
+                m |= 1u << 15;
+            } else {
+                if (x < nlow[a]) m |= 1u << (slot[a] + x);
+                if (x >= nfirst[a]) m |= 1u << (slot[a] + nlow[a] + x - nfirst[a]);
+            }
+        }
+        return m;
     }
 
     // Table `idx` of the workgroup: 16 bf16 slots per block of the box, as the waves
@@ -235,17 +251,7 @@ struct MaskRows {
         for (int row = lane; row < g.tab_rows; row += kWave) {
             int oc[kMaxRank], inner0;
             box.block_coords(row, oc, inner0);
-            unsigned m = row < box.nb ? 0u : 1u << 15;
-#pragma unroll
-            for (int a = 0; a < R - 1; ++a) {
-                const int x = oc[a] - lo[a];
-                if ((unsigned)x >= (unsigned)len[a]) {
-                    m |= 1u << 15;
-                } else {
-                    if (x < nlow[a]) m |= 1u << (slot[a] + x);
-                    if (x >= nfirst[a]) m |= 1u << (slot[a] + nlow[a] + x - nfirst[a]);
-                }
-            }
+            const unsigned m = row < box.nb ? row_slots(oc) : 1u << 15;
             st16<i32x4>(tab + row * 32, expand(m, kMaskRow));
             st16<i32x4>(tab + row * 32 + 16, expand(m >> 8, kMaskRow));
         }
@@ -253,8 +259,8 @@ struct MaskRows {
 
     // Mask operand of a token, slots 8 grp .. 8 grp + 7: start with operand(), then
     // axis by axis the token's own range [first, last] of box positions.
-    __device__ __forceinline__ static unsigned operand() { return 1u << 15; }
-    __device__ __forceinline__ unsigned operand(unsigned m, int a, int first, int last) const {
+    NA_HD static unsigned operand() { return 1u << 15; }
+    NA_HD unsigned operand(unsigned m, int a, int first, int last) const {
         const int nh = len[a] - nfirst[a];
         const int miss = min(max(first - lo[a], 0), nlow[a]);           // first positions missed
         const int have = min(max(last + 1 - lo[a] - nfirst[a], 0), nh);  // last ones reached

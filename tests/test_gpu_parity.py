@@ -464,6 +464,29 @@ def test_backward_split_and_single_launch(na, force, ext, ks, ds, cs, D, dtype, 
         assert torch.equal(a, b)
 
 
+# Unforced, a 1-D backward with a long window is split from a grid of 4096 workgroups (2048 at
+# D = 128): the last problem below and the first at or above, three slices against the oracle.
+@pytest.mark.parametrize("D,dtype,BH,m,nwg", [
+    (32, "fp16", 819, 2, 4095), (32, "fp16", 820, 2, 4100), (64, "bf16", 819, 2, 4095),
+    (64, "bf16", 820, 2, 4100), (128, "bf16", 204, 1, 2040), (128, "bf16", 205, 1, 2050)])
+def test_backward_split_on_large_1d_grids(na, D, dtype, BH, m, nwg):
+    L, kk, cs = 640, 512, (True,)
+    t = na.current_tiling((L,), (kk,), (1,), 1, BH, D, TDT[dtype], causal=cs, forward=False)
+    per_wg = t.wave_tile[0] * t.waves[0]
+    assert t.blocks_per_wave == m and BH * -(-L // per_wg) == nwg, t
+    gen = torch.Generator(device="cuda").manual_seed(61)
+    q, k, v, g = (torch.randn((1, BH, L, D), generator=gen, device="cuda").to(TDT[dtype])
+                  for _ in range(4))
+    out, lse = na.forward(q, k, v, kk, 1, causal=cs)
+    grads = na.backward(q, k, v, out, lse, g, kk, 1, causal=cs)
+    pick = [0, BH // 2, BH - 1]
+    refs = oracle.backward(*(_f64(x[:, pick]) for x in (q, k, v, g)), (kk,), (1,),
+                           1.0 / math.sqrt(D), causal=cs)
+    e = [_maxerr(x[:, pick], r) for x, r in zip(grads, refs)]
+    _log(f"bwd 1-D grid {nwg} D={D} {dtype}: max err dq/dk/dv = {[f'{x:.3g}' for x in e]}")
+    assert max(e) <= TOL[dtype]
+
+
 def test_backward_deterministic(na):
     shape = (1, 2, 30, 27, 64)
     q, k, v, g = _dev(*_inputs(shape, "bf16", 22, 4))
@@ -718,15 +741,20 @@ def test_every_candidate_tiling_matches_the_oracle(na, ext, ks, ds, cs, D, dtype
 
 
 # The narrow form (two-block tilings whose halo rows fit one 16-key block and whose waves can be
-# cut to eight columns of them): window and tile shapes at its limits, axes as short as the window
+# cut to eight columns of them; test_narrow_host.py checks that each is): window and tile shapes at its limits, axes as short as the window
 # or shorter than a tile, unequal groups, causal axes, scales of either sign and zero, and keys
 # whose scores would swamp every neighbour's if a mask let them through.
 NARROW_CASES = [
     # (extents, kernel, dilation, causal, head_dim, dtype, wave tile, waves, scale, swamp)
     ((9, 13, 21), (7, 7, 7), (1, 1, 1), None, 64, "fp16", (2, 2, 8), (2, 2, 1), None, False),
     ((7, 14, 30), (7, 7, 7), (1, 2, 3), None, 64, "bf16", (2, 2, 8), (2, 2, 1), None, True),
-    ((11, 9, 16), (5, 3, 7), (1, 1, 2), (True, False, True), 32, "fp16", (2, 2, 8), (2, 2, 1),
-     None, False),
+    ((11, 13, 16), (5, 7, 5), (1, 1, 2), (True, False, True), 32, "fp16", (2, 2, 8), (2, 2, 1),
+     None, True),
+    ((9, 14, 30), (7, 7, 7), (1, 2, 3), None, 64, "fp16", (2, 2, 8), (2, 2, 1), None, True),
+    ((25, 39), (11, 5), (1, 3), (False, True), 32, "fp16", (4, 8, 1), (4, 1, 1), None, True),
+    ((44, 37), (11, 5), (3, 2), None, 64, "fp16", (4, 8, 1), (4, 1, 1), 0.2, True),
+    ((33, 40), (13, 1), (1, 2), None, 64, "bf16", (4, 8, 1), (4, 1, 1), None, False),
+    ((9, 8, 16), (5, 7, 6), (1, 1, 1), None, 128, "fp16", (2, 2, 8), (2, 2, 1), -0.1, True),
     ((6, 8, 19), (3, 7, 5), (2, 1, 1), (False, True, False), 128, "bf16", (2, 2, 8), (2, 2, 1),
      None, True),
     ((4, 5, 11), (4, 5, 6), (1, 1, 1), None, 64, "fp16", (2, 2, 8), (2, 2, 1), None, False),
@@ -734,11 +762,16 @@ NARROW_CASES = [
     ((44, 37), (11, 5), (3, 2), (True, False), 64, "bf16", (4, 8, 1), (4, 1, 1), -0.2, True),
     ((40, 24), (9, 4), (1, 1), (False, True), 32, "bf16", (4, 8, 1), (4, 1, 1), 0.0, False),
     ((30, 9), (30, 3), (1, 1), None, 64, "fp16", (4, 8, 1), (4, 1, 1), -0.1, False),
+]
+# the other side of the rule: it would save no tile, so the ordinary form runs
+NARROW_EDGE_CASES = [
+    ((11, 9, 16), (5, 3, 7), (1, 1, 2), (True, False, True), 32, "fp16", (2, 2, 8), (2, 2, 1),
+     None, False),
     ((17, 23), (2, 1), (1, 1), None, 64, "fp16", (4, 8, 1), (4, 1, 1), None, False),
 ]
 
 
-@pytest.mark.parametrize("ext,ks,ds,cs,D,dtype,wt,wg,scale,swamp", NARROW_CASES)
+@pytest.mark.parametrize("ext,ks,ds,cs,D,dtype,wt,wg,scale,swamp", NARROW_CASES + NARROW_EDGE_CASES)
 def test_narrow_form(na, force, ext, ks, ds, cs, D, dtype, wt, wg, scale, swamp):
     force(NA_BWD_SPLIT=1)  # (the backward's dQ launch has the form too)
     q, k, v, g = _inputs((2, 2) + ext + (D,), dtype, 47, 4)
@@ -751,13 +784,20 @@ def test_narrow_form(na, force, ext, ks, ds, cs, D, dtype, wt, wg, scale, swamp)
     out, lse = na.forward(qd, kd, vd, ks, ds, scale=sc, causal=cs, tiling=t)
     ro, rl = oracle.forward(fq, fk, fv, ks, ds, sc, causal=cs)
     e = [_maxerr(out, ro), _maxerr(lse, rl)]
+    e_s = _score_error(dtype, D, fq, fk, ks, ds, abs(sc), cs)
+    if swamp and dtype == "fp16" and D <= 64:
+        # scores of up to 400 from a Q rounded after its scaling: each moves by at most e_s, so
+        # a logsumexp by e_s and a probability by a factor of e^(2 e_s)
+        pv, _ = oracle.forward(fq, fk, np.abs(fv), ks, ds, sc, causal=cs)
+        e = [float((np.abs(_f64(x) - r) / b).max()) * TOL[dtype] for x, r, b in (
+            (out, ro, 1 + np.expm1(2 * e_s) * pv / TOL[dtype]),
+            (lse, rl, 1 + e_s[..., 0] / TOL[dtype]))]
     # the backward operator from the oracle's stored results; a score sums D products in fp32,
     # D roundings at most, each relative to the sum of their absolute values
     so, sl = torch.from_numpy(ro).to(TDT[dtype]), torch.from_numpy(rl).float()
     grads = na.backward(qd, kd, vd, *_dev(so, sl), gd, ks, ds, scale=sc, causal=cs, tiling=t)
     refs = oracle.backward_given(fq, fk, fv, _f64(so), _f64(sl), fg, ks, ds, sc, causal=cs,
                                  abs_sums=True)
-    e_s = _score_error(dtype, D, fq, fk, ks, ds, abs(sc), cs)
     e_s = e_s + D * _score_error("bf16", D, fq, fk, ks, ds, abs(sc), cs)
     terms = [np.abs(a) for a in refs[3:]]  # (the oracle's carry the scale's sign)
     bound = _operator_bound(dtype, D, int(np.prod(ks)), e_s, refs[:3], terms)
