@@ -60,7 +60,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
     using C = DqCfg<R, D, T, SB>;
     constexpr bool kNar = SHORT == 2;
     constexpr int Q = kNar ? 32 : 16, QM = kNar ? 1 : QM_;
-    using Ops = TileOps<T, D, Q, kNar>;
+    using Ops = TileOps<T, D, Q>;
     using x8 = typename Tr<T>::x8;
     constexpr int kRowB = Rows<T, D>::kRowBytes;
     constexpr int kN = Tile<Q>::kN;
@@ -201,7 +201,7 @@ __device__ __forceinline__ void dq_role(const Geo& g, int braw, unsigned char* s
 #pragma unroll
             for (int r = 0; r < kN; ++r) {
                 const int ib = halo.nbr == 2 ? bi : 0;
-                const int pos = kNar ? col0 + grp * 4 + (r & 3) : ib * 16 + score_row(r, grp);
+                const int pos = kNar ? col0 + grp * 4 + (r & 3) : ib * 16 + grp * 4 + r;
                 ain[m].set(bi, r, (unsigned)(pos - qs[m][R - 1]) < (unsigned)g.k[R - 1]
                                       ? -lse2[m]
                                       : -INFINITY);

@@ -139,7 +139,7 @@ __device__ __forceinline__ typename Tr<T>::x8 zero_x8() {
 
 // Result tile of 32 tokens (rows) x Q tokens (columns): what a wave holds of
 // one pair of 16-token row blocks.  Lane l has column l % Q and, of row block
-// bi, kN rows: entry r is row score_row(r, l / Q) of the block.
+// bi, kN rows: entry r is row 8 (r / 4) + 4 (l / Q) + r % 4 of the block.
 template <int Q>
 struct Tile;
 template <>
@@ -165,7 +165,6 @@ __device__ __forceinline__ Tile<Q> splat_tile(float x) {
         for (int r = 0; r < Tile<Q>::kN; ++r) t.set(bi, r, x);
     return t;
 }
-__device__ __forceinline__ int score_row(int r, int grp) { return (r >> 2) * 8 + grp * 4 + (r & 3); }
 
 // Store four fp32 values rounded to T at p (8 or 16 bytes).
 template <typename T>

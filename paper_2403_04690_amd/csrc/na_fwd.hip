@@ -57,21 +57,24 @@ struct FwdCfg {
 // Waves per SIMD the register allocation must allow: four for the 16-bit
 // kernels that fit 128 VGPRs (every one at D <= 64, and the one-block ones at
 // D = 128); the others take what they need.
-template <int D, typename T, int Q, int QM>
+template <int D, typename T, int QM>
 constexpr int fwd_min_waves() {
-    return sizeof(T) == 2 && (D <= 64 || (Q == 16 && QM == 1)) ? 4 : 1;
+    return sizeof(T) == 2 && (D <= 64 || QM == 1) ? 4 : 1;
 }
 
 // c = scale * log2(e): scores are kept in base 2.  SHORT = 1: every halo row
 // holds at most two 16-key blocks (rank >= 2), so the inner-axis mask is a
 // per-lane constant; SHORT = 0: general masking with mask-free full blocks.
-template <int R, int D, typename T, int Q, int QM, int SB, int SHORT, int W>
-__global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_fwd_kernel(
+// QM_ blocks of 16 queries per wave on 16x16x32 steps; SHORT = 2: the narrow form of a
+// two-block tiling, one block of 32 queries on 32x32x16 steps (narrow_form).
+template <int R, int D, typename T, int QM_, int SB, int SHORT, int W>
+__global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, QM_>())) void na_fwd_kernel(
     Geo g, const T* __restrict__ qg, const T* __restrict__ kg, const T* __restrict__ vg,
     T* __restrict__ og, float* __restrict__ lseg, float c) {
     using C = FwdCfg<R, D, T, SB, W>;
-    constexpr bool kNar = SHORT == 2;  // narrow form
-    using Ops = TileOps<T, D, Q, kNar>;
+    constexpr bool kNar = SHORT == 2;
+    constexpr int Q = kNar ? 32 : 16, QM = kNar ? 1 : QM_;
+    using Ops = TileOps<T, D, Q>;
     using x8 = typename Tr<T>::x8;
     extern __shared__ __align__(16) unsigned char smem_raw[];
 
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(W * kWave, (fwd_min_waves<D, T, Q, QM>())) void na_
 #pragma unroll
                 for (int r = 0; r < Tile<Q>::kN; ++r) {
                     const int ib = halo.nbr == 2 ? bi : 0;
-                    const int pos = kNar ? col0 + grp * 4 + (r & 3) : ib * 16 + score_row(r, grp);
+                    const int pos = kNar ? col0 + grp * 4 + (r & 3) : ib * 16 + grp * 4 + r;
                     const bool v = (unsigned)(pos - qs[m][R - 1]) < (unsigned)g.k[R - 1];
                     ain[m].set(bi, r, v ? negm[m] : -INFINITY);
                 }
@@ -514,26 +517,30 @@ static int max_row_blocks(const Geo& g, int rank) {
     return (e + 15) / 16;
 }
 
-template <int R, int D, typename T, int Q, int QM, int SB, int W = 4>
+template <int R, int D, typename T, int QM, int SB, int W = 4>
 static hipError_t launch_fwd_inst(const Geo& g0, const void* q, const void* k, const void* v,
                                   void* o, float* lse, float scale, hipStream_t stream) {
     using C = FwdCfg<R, D, T, SB, W>;
     // The register bound asks for no more workgroups (of W waves, over the CU's
     // four SIMDs) than its 160 KiB of LDS holds, with double buffers (stages of
-    // 16 blocks are used only when the halo fits in one: single).
-    static_assert(fwd_min_waves<D, T, Q, QM>() * 4 / W * (SB >= 16 ? 1 : 2) * C::kBufBytes <= 160 * 1024,
+    // 16 blocks are used only when the halo fits in one: single) and 8 KiB of mask
+    // tables.  (Larger ones leave three workgroups per CU at D = 64, which still is the
+    // faster: 9 x 9 x 5 windows, tables of 9 KiB, 250 us in the ordinary form, 191 so.)
+    constexpr size_t kTab = R > 1 && sizeof(T) == 2 && QM == 2 ? 8192 : 0;
+    static_assert(fwd_min_waves<D, T, QM>() * 4 / W *
+                          ((SB >= 16 ? 1 : 2) * C::kBufBytes + kTab) <= 160 * 1024,
                   "register bound beyond the LDS occupancy");
     if (g0.WGd[0] * g0.WGd[1] * g0.WGd[2] != W) return hipErrorInvalidConfiguration;
     const bool short_rows = R > 1 && max_row_blocks(g0, R) <= 2;
-    auto kern = na_fwd_kernel<R, D, T, Q, QM, SB, 0, W>;
+    auto kern = na_fwd_kernel<R, D, T, QM, SB, 0, W>;
     if constexpr (R > 1)  // (1-D halos have one row: never short)
-        if (short_rows) kern = na_fwd_kernel<R, D, T, Q, QM, SB, 1, W>;
+        if (short_rows) kern = na_fwd_kernel<R, D, T, QM, SB, 1, W>;
     const int nb_max = max_halo_blocks(g0, R);
     size_t lds = (nb_max > SB ? 2 : 1) * C::kBufBytes;
     Geo g = g0;
     if constexpr (R > 1 && sizeof(T) == 2 && QM == 2) {
         if (narrow_form(g, R, nb_max)) {
-            kern = na_fwd_kernel<R, D, T, 32, 1, SB, 2, W>;
+            kern = na_fwd_kernel<R, D, T, QM, SB, 2, W>;
             g.tab_off = (int)lds;
             lds += mask_table_bytes(g, R);
         }
@@ -553,8 +560,8 @@ template <int R, int D, typename T>
 static hipError_t launch_fwd_qm(const Geo& g, int qm, const void* q, const void* k, const void* v,
                                 void* o, float* lse, float scale, hipStream_t stream) {
     if constexpr (sizeof(T) == 4) {
-        if (qm == 1) return launch_fwd_inst<R, D, T, 16, 1, 2>(g, q, k, v, o, lse, scale, stream);
-        return launch_fwd_inst<R, D, T, 16, 2, 2>(g, q, k, v, o, lse, scale, stream);
+        if (qm == 1) return launch_fwd_inst<R, D, T, 1, 2>(g, q, k, v, o, lse, scale, stream);
+        return launch_fwd_inst<R, D, T, 2, 2>(g, q, k, v, o, lse, scale, stream);
     } else {
         // One block per wave at D = 128: stages of half the keys, so that the
         // four waves per SIMD the registers allow also fit in LDS.
@@ -563,19 +570,19 @@ static hipError_t launch_fwd_qm(const Geo& g, int qm, const void* q, const void*
         if constexpr (R == 1) {
             if (g.WGd[0] == 8) {
                 if (qm == 1)
-                    return launch_fwd_inst<R, D, T, 16, 1, kSB1 * 2, 8>(g, q, k, v, o, lse, scale, stream);
-                return launch_fwd_inst<R, D, T, 16, 2, 8, 8>(g, q, k, v, o, lse, scale, stream);
+                    return launch_fwd_inst<R, D, T, 1, kSB1 * 2, 8>(g, q, k, v, o, lse, scale, stream);
+                return launch_fwd_inst<R, D, T, 2, 8, 8>(g, q, k, v, o, lse, scale, stream);
             }
         }
         // one LDS stage covering the whole halo when it is small and D is 32
         if constexpr (D == 32) {
             if (max_halo_blocks(g, R) <= 16) {
-                if (qm == 1) return launch_fwd_inst<R, D, T, 16, 1, 16>(g, q, k, v, o, lse, scale, stream);
-                return launch_fwd_inst<R, D, T, 16, 2, 16>(g, q, k, v, o, lse, scale, stream);
+                if (qm == 1) return launch_fwd_inst<R, D, T, 1, 16>(g, q, k, v, o, lse, scale, stream);
+                return launch_fwd_inst<R, D, T, 2, 16>(g, q, k, v, o, lse, scale, stream);
             }
         }
-        if (qm == 1) return launch_fwd_inst<R, D, T, 16, 1, kSB1>(g, q, k, v, o, lse, scale, stream);
-        return launch_fwd_inst<R, D, T, 16, 2, 4>(g, q, k, v, o, lse, scale, stream);
+        if (qm == 1) return launch_fwd_inst<R, D, T, 1, kSB1>(g, q, k, v, o, lse, scale, stream);
+        return launch_fwd_inst<R, D, T, 2, 4>(g, q, k, v, o, lse, scale, stream);
     }
 }
 

@@ -544,10 +544,9 @@ struct ColFrag {
     }
 };
 
-// The same two reads for the 32x32x16 steps (16-bit types, tiles of 32 rows).
-// Row r of a tile is staged row r, or with NARROW the rows of a tile are eight
-// columns (col0 .. col0 + 7) of four consecutive 16-row blocks: staged row
-// 16 (r / 8) + col0 + r % 8.
+// The same two reads for the 32x32x16 steps of the narrow form (16-bit types).  The 32
+// rows of a tile are eight columns (col0 .. col0 + 7) of four consecutive 16-row blocks:
+// row r is staged row 16 (r / 8) + col0 + r % 8.
 // Row fragment st: lane l holds row l % 32, elements st * 16 + 8 (l / 32) .. +7.
 // One offset per lane: fragment st's segment is that of fragment 0 with bits of
 // st flipped in, (2 st + l / 32) ^ swz = 2 st ^ (l / 32 ^ swz), so its offset is
@@ -558,10 +557,9 @@ struct RowFrag32 {
     using L = Rows<T, D>;
     static constexpr int kKS = D / 16;
     int off;
-    template <bool NARROW>
     __device__ __forceinline__ void init(int lane, int col0) {
         const int r = lane & 31;
-        off = L::off(NARROW ? (r >> 3) * 16 + col0 + (r & 7) : r, lane >> 5);
+        off = L::off((r >> 3) * 16 + col0 + (r & 7), lane >> 5);
     }
     __device__ __forceinline__ void read(const unsigned char* tile,
                                          typename Tr<T>::x8 (&f)[kKS]) const {
@@ -572,25 +570,24 @@ struct RowFrag32 {
     }
 };
 
-// Transposed fragment of columns d = db * 32 + l % 32 against the 16 rows of
-// block bi: slot j of lane l is row 4 (l / 32) + j (j < 4) or
-// 8 + 4 (l / 32) + j - 4 (j >= 4) of the block, the rows that lane holds of a
-// 32x32 result tile, so such a tile feeds the next product without a shuffle.
-// (Again one offset per lane: column block db flips segment bits, and the second
-// row of a fragment lies in the next row group, where the swizzle flips bits too.)
-template <typename T, int D, bool NARROW>
+// Transposed fragment of columns d = db * 32 + l % 32 against rows 16 bi .. +15 of the
+// tile: slot j of lane l is row 4 (l / 32) + j (j < 4) or 8 + 4 (l / 32) + j - 4
+// (j >= 4) of them, the rows that lane holds of a 32x32 result tile, so such a tile
+// feeds the next product without a shuffle.
+// (Again one offset per lane: column block db flips segment bits, and slots 4 .. 7 lie
+// in the next 16-row block, with the same swizzle.)
+template <typename T, int D>
 struct ColFrag32 {
     static_assert(sizeof(T) == 2, "16-bit types");
     using L = Rows<T, D>;
     static constexpr int kDB = D / 32;
-    static constexpr int kBlk = (NARROW ? 32 : 16) * L::kRowBytes;  // from bi = 0 to bi = 1
-    static constexpr int kSec = (NARROW ? 16 : 8) * L::kRowBytes;   // to slots 4 .. 7
-    static constexpr int kSecFlip = NARROW ? 0 : L::swz(8) << 4;
+    static constexpr int kBlk = 32 * L::kRowBytes;  // from bi = 0 to bi = 1
+    static constexpr int kSec = 16 * L::kRowBytes;  // to slots 4 .. 7
     int off;
     __device__ __forceinline__ void init(int lane, int col0) {
         // 16-lane group (2 h + e): rows 4 h + s, columns db * 32 + e * 16 + 4 q .. +3
         const int h = lane >> 5, e = (lane >> 4) & 1, i = lane & 15;
-        const int r = (NARROW ? col0 : 0) + 4 * h + (i >> 2), q = i & 3;
+        const int r = col0 + 4 * h + (i >> 2), q = i & 3;
         off = L::off(r, (e * 16 + 4 * q) / 8) + (q & 1) * 8;
     }
     // Every fragment of the tile, (db, bi) at 2 db + bi, and the wait for them, in
@@ -608,14 +605,14 @@ struct ColFrag32 {
         if constexpr (kDB == 1) {
             i32x2 r[4];
             asm volatile(
-                "ds_read_b64_tr_b16 %0, %4 offset:%6\n\t"
-                "ds_read_b64_tr_b16 %1, %5 offset:%7\n\t"
-                "ds_read_b64_tr_b16 %2, %4 offset:%8\n\t"
-                "ds_read_b64_tr_b16 %3, %5 offset:%9\n\t"
+                "ds_read_b64_tr_b16 %0, %4 offset:%5\n\t"
+                "ds_read_b64_tr_b16 %1, %4 offset:%6\n\t"
+                "ds_read_b64_tr_b16 %2, %4 offset:%7\n\t"
+                "ds_read_b64_tr_b16 %3, %4 offset:%8\n\t"
                 "s_waitcnt lgkmcnt(0)"
                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
-                : "v"((lds_u8*)(tile + o)), "v"((lds_u8*)(tile + (o ^ kSecFlip))), "n"(EXTRA),
-                  "n"(EXTRA + kSec), "n"(EXTRA + kBlk), "n"(EXTRA + kBlk + kSec)
+                : "v"((lds_u8*)(tile + o)), "n"(EXTRA), "n"(EXTRA + kSec), "n"(EXTRA + kBlk),
+                  "n"(EXTRA + kBlk + kSec)
                 : "memory");
 #pragma unroll
             for (int i = 0; i < 2; ++i) f[i] = cat(r[2 * i], r[2 * i + 1]);
@@ -625,20 +622,19 @@ struct ColFrag32 {
                 const int o0 = o ^ (db << 6), o1 = o ^ ((db + 1) << 6);
                 i32x2 r[8];
                 asm volatile(
-                    "ds_read_b64_tr_b16 %0, %8 offset:%12\n\t"
-                    "ds_read_b64_tr_b16 %1, %9 offset:%13\n\t"
-                    "ds_read_b64_tr_b16 %4, %10 offset:%12\n\t"
-                    "ds_read_b64_tr_b16 %5, %11 offset:%13\n\t"
-                    "ds_read_b64_tr_b16 %2, %8 offset:%14\n\t"
-                    "ds_read_b64_tr_b16 %3, %9 offset:%15\n\t"
-                    "ds_read_b64_tr_b16 %6, %10 offset:%14\n\t"
-                    "ds_read_b64_tr_b16 %7, %11 offset:%15\n\t"
+                    "ds_read_b64_tr_b16 %0, %8 offset:%10\n\t"
+                    "ds_read_b64_tr_b16 %1, %8 offset:%11\n\t"
+                    "ds_read_b64_tr_b16 %4, %9 offset:%10\n\t"
+                    "ds_read_b64_tr_b16 %5, %9 offset:%11\n\t"
+                    "ds_read_b64_tr_b16 %2, %8 offset:%12\n\t"
+                    "ds_read_b64_tr_b16 %3, %8 offset:%13\n\t"
+                    "ds_read_b64_tr_b16 %6, %9 offset:%12\n\t"
+                    "ds_read_b64_tr_b16 %7, %9 offset:%13\n\t"
                     "s_waitcnt lgkmcnt(0)"
                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]),
                       "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-                    : "v"((lds_u8*)(tile + o0)), "v"((lds_u8*)(tile + (o0 ^ kSecFlip))),
-                      "v"((lds_u8*)(tile + o1)), "v"((lds_u8*)(tile + (o1 ^ kSecFlip))),
-                      "n"(EXTRA), "n"(EXTRA + kSec), "n"(EXTRA + kBlk), "n"(EXTRA + kBlk + kSec)
+                    : "v"((lds_u8*)(tile + o0)), "v"((lds_u8*)(tile + o1)), "n"(EXTRA),
+                      "n"(EXTRA + kSec), "n"(EXTRA + kBlk), "n"(EXTRA + kBlk + kSec)
                     : "memory");
 #pragma unroll
                 for (int i = 0; i < 4; ++i) f[2 * db + i] = cat(r[2 * i], r[2 * i + 1]);
@@ -660,11 +656,11 @@ struct ColFrag32 {
 //   cols(): transposed, contraction along the 32 rows;
 //   scores(): s += rows x (register fragments b[]);
 //   accum(): acc[] += cols^T x p, p the tile's values rounded to T.
-template <typename T, int D, int Q, bool NARROW = false>
+template <typename T, int D, int Q>
 struct TileOps;
 
 template <typename T, int D>
-struct TileOps<T, D, 16, false> {
+struct TileOps<T, D, 16> {
     using x8 = typename Tr<T>::x8;
     using Acc = f32x4;
     static constexpr int kStep = 32, kKS = D / 32, kDB = D / 16, kF = D / 16, kPF = 1;
@@ -718,15 +714,15 @@ struct TileOps<T, D, 16, false> {
     }
 };
 
-template <typename T, int D, bool NARROW>
-struct TileOps<T, D, 32, NARROW> {
+template <typename T, int D>
+struct TileOps<T, D, 32> {
     using x8 = typename Tr<T>::x8;
     using Acc = f32x16;
     static constexpr int kStep = 16, kKS = D / 16, kDB = D / 32, kF = D / 16, kPF = 2;
     RowFrag32<T, D> rf;
-    ColFrag32<T, D, NARROW> cf;
-    __device__ __forceinline__ void init(int lane, int col0 = 0) {
-        rf.template init<NARROW>(lane, col0);
+    ColFrag32<T, D> cf;
+    __device__ __forceinline__ void init(int lane, int col0) {
+        rf.init(lane, col0);
         cf.init(lane, col0);
     }
     __device__ __forceinline__ void rows(const unsigned char* tile, x8 (&f)[kF]) const {

@@ -54,8 +54,8 @@ def test_forward_kernels_keep_their_operands_in_registers(tmp_path):
     if not kernels:
         pytest.skip("a library without device code")
     fwd = {s: n for s, n in kernels if "na_fwd_kernel" in s}
-    # <rank, D, type, queries per block, blocks per wave, stage blocks, row form, waves>
-    narrow = {s: n for s, n in fwd.items() if "Li32ELi1ELi" in s}
+    # <rank, D, type, blocks per wave, stage blocks, row form (2: narrow), waves>
+    narrow = {s: n for s, n in fwd.items() if re.search(r"Li2ELi\d+ELi2ELi4EEEv", s)}
     assert len(fwd) > 60 and len(narrow) == 16, (len(fwd), len(narrow))
     # up to six values that only the epilogue reads (offsets, row sums); operands take more
     assert {s: n for s, n in fwd.items() if n > 6} == {}
