@@ -43,7 +43,8 @@ WORKLOAD = workloads.BENCH_WORKLOAD
 PEAK_FP16_TFLOPS = 2516.6   # MI355X dense fp16 MFMA
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 PMC_FILE = os.path.join(ROOT, "profiles", "na_fwd_kernel.2d_fp16_56x56_k7.pmc.txt")
-FWD_SOURCES = ["na_fwd.hip", "na_common.h", "na_stage.h", "na_index.h", "na_fastdiv.h"]
+FWD_SOURCES = ["na_fwd.hip", "na_common.h", "na_stage.h", "na_index.h", "na_fastdiv.h",
+               "na_launch.h"]
 
 
 def fwd_source_digest():

@@ -874,10 +874,10 @@ __device__ __forceinline__ void dkdv_role(const Geo& g, int braw, int nwk,
 // 64 queries instead (about 34 KiB), which leaves room for the third wave,
 // and D = 32 stages 128 (about 34 KiB): four waves at rank 1, three above.
 // D = 128 (rank 1, one block per wave) stages 32 queries or keys, so that the
-// three waves its registers allow (152-166 VGPRs) fit in LDS: 1-D causal k = 512
-// bf16 training step 275 -> 246 us against the single launch, which holds O rows
-// in LDS too, waits at a second barrier per stage and runs the dQ role at the
-// occupancy of the other.
+// three waves its registers allow (152-166 VGPRs) fit in LDS.  The single launch
+// stages 32 keys in its dQ role too (SBQ in launch_bwd_inst), which takes its LDS
+// from 64 to 48 KiB: 1-D 8192 x 16 heads k = 255 fp16 143 -> 128 us, 32768 x 8 k = 127
+// 236 -> 212 us.
 // Where the split form exists: 16-bit types at D <= 64, and at D = 128 for rank 1 with
 // one block per wave.
 template <int R, int D, typename T, int M>

@@ -287,7 +287,7 @@ struct MaskRows {
 // LDS rows: D elements of T per token, row-major and unpadded, cut into
 // 16-byte segments; segment s of row r is stored at position s ^ swz(r).
 // The swizzle is linear in the low four row bits and was chosen so that both
-// fragment reads below are free of bank conflicts:
+// reads of 16-row fragments below are free of bank conflicts:
 //   * 16-byte reads of one segment down 16 consecutive rows (MFMA operands
 //     whose contraction runs along D);
 //   * transposed 8-byte reads of 4 consecutive rows x 2 adjacent segments per
@@ -297,6 +297,9 @@ struct MaskRows {
 //     cycles were conflicts, with those of this swizzle none).  Conflict-free
 //     reads took the dK/dV launch of the 1-D k = 1023 backward from 352 to
 //     336 us and its dQ launch from 258 to 244 us.
+// The narrow form's reads (RowFrag32, ColFrag32) are not: their eight-column rows start
+// anywhere in a block, and rows 16 apart share a swizzle (counted on 16 x 64 x 64, 7^3 fp16:
+// 31 % of the LDS cycles of the forward and 38 % of dQ's are conflicts).
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 struct Rows {
@@ -652,10 +655,10 @@ struct ColFrag32 {
 // The fragments and products of one tile, 32 staged rows (two 16-row blocks)
 // against a block of Q tokens held in registers, by Q.  kF fragments cover the
 // 32 rows in either orientation.
-//   frag / rows(): the tile's rows as A operand, contraction along D;
+//   rows(): the tile's rows as A operand, contraction along D;
 //   cols(): transposed, contraction along the 32 rows;
-//   scores(): s += rows x (register fragments b[]);
-//   accum(): acc[] += cols^T x p, p the tile's values rounded to T.
+//   score(): s += a row fragment x the register fragments b[];
+//   accum(): acc[] += a transposed fragment x p, p the tile's values rounded to T.
 template <typename T, int D, int Q>
 struct TileOps;
 
